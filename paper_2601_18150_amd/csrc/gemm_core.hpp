@@ -167,6 +167,19 @@ __device__ __forceinline__ void wait_dma_step(int later) {
   }
 }
 
+// The same for a ring of D slots that one wave refills itself, `later` further
+// fetches of kPer instructions each issued behind the one waited for.
+template <int kPer, int D>
+__device__ __forceinline__ void wait_own_ring(int later) {
+  static_assert((D - 1) * kPer < 64, "vmcnt is 6 bits");
+  if constexpr (D > 1) {
+    if (later >= D - 1) { wait_vmcnt<(D - 1) * kPer>(); return; }
+    wait_own_ring<kPer, D - 1>(later);
+  } else {
+    wait_vmcnt<0>();
+  }
+}
+
 // One output tile to compute (wave-uniform values, produced by a job provider).
 struct TileJob {
   int row_lo;              // first row of A / Y

@@ -46,17 +46,6 @@ struct SmallCfg {
   static_assert(kLds <= 160 * 1024 && (D_ - 1) * kPer < 64, "LDS is 160 KiB, vmcnt 6 bits");
 };
 
-// Wait until at most `later` (< D) K blocks' DMA instructions are outstanding.
-template <int kPer, int D>
-__device__ __forceinline__ void small_wait(int later) {
-  if constexpr (D > 1) {
-    if (later >= D - 1) { wait_vmcnt<(D - 1) * kPer>(); return; }
-    small_wait<kPer, D - 1>(later);
-  } else {
-    wait_vmcnt<0>();
-  }
-}
-
 // kRows weight rows from wbase (swrow: their block's scales per K block) times
 // `m` tokens: this lane moves row arow[o] (a byte offset from qa) of activation
 // octet o and the scale of token srow (an index into each row of sa); output
@@ -107,7 +96,7 @@ __device__ __forceinline__ void small_tile(const uint8_t* __restrict__ wbase, ui
   int slot = 0;
   for (int i = 0; i < nb; ++i) {
     const float swv = swrow[wk + i * C::WK];
-    small_wait<C::kPer, C::D>(nb - 1 - i);
+    wait_own_ring<C::kPer, C::D>(nb - 1 - i);
     asm volatile("" ::: "memory");
     const uint8_t* st = ring + slot * C::kSlot;
     const uint8_t* sta = st + 2 * C::TN * 1024;

@@ -18,7 +18,7 @@
 //            widened exactly to bf16) by v_mfma_f32_16x16x16_bf16, 16 per page;
 //            the score layout of the first product is already the P operand
 //            layout of the second;
-//   each wave covers one split of the sequence; a second kernel merges the
+//   a workgroup covers one split of the sequence; a second kernel merges the
 //   splits (log-sum-exp weights) and applies v_scale.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gemm_core.hpp"
 #include "launch.hpp"
 
 namespace fp8rl {
@@ -184,22 +185,15 @@ __device__ __forceinline__ v4i16_t to_bf16x4(uint32_t c) {
 }
 __device__ __forceinline__ v4i16_t to_bf16x4(const uint2& c) { return __builtin_bit_cast(v4i16_t, c); }
 
-// Per lane and page: keys = 32 contiguous cache values (token L % 16, dims 32 (L / 16) ..),
-// values = 32 contiguous cache values (tokens 4 (L / 16) .. +3 of dims 8 (L % 16) .. +7).
-template <bool kFp8>
-struct PageRegs;
-template <>
-struct PageRegs<true> {
-  uint4 k[2];
-  uint4 v[2];
-};
-template <>
-struct PageRegs<false> {
-  uint4 k[4];
-  uint4 v[4];
-};
-
 __device__ __forceinline__ float shfl_xor_f(float v, int m) { return __shfl_xor(v, m, 64); }
+
+// Max over the four lanes with the same L % 16 (lane-row swaps, no LDS traffic).
+__device__ __forceinline__ float max_over_rows(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 
 // Partial record per (sequence, kv head, split): o[G][128], then m[G], l[G],
 // padded to a multiple of 4 floats (16-byte aligned records).
@@ -210,40 +204,102 @@ constexpr int rec_m() { return kG * kDim; }
 template <int kG>
 constexpr int rec_l() { return kG * kDim + kG; }
 
-// Workgroup = 4 waves = 4 consecutive splits of one (sequence, kv head); wave w
-// covers tokens [split * split_tokens, +split_tokens) of the sequence.  Lane L,
-// g = L / 16, j = L % 16:
+// Workgroup = 4 waves on one split of one (sequence, kv head): wave w attends over
+// pages w, w + 4, ... of the split's split_pages pages, and the four results are
+// combined in LDS at the end, so a split leaves one record (or, when the whole
+// sequence is one split, the output itself).
+//
+// Pages go from the cache to LDS by DMA, whole 1 KiB runs per instruction, into a
+// ring of kDepth pages that only this wave touches: no barrier in the loop, each
+// wave waits for its own DMA by count, and a page's slot is refilled as soon as
+// its fragments are in registers.  Loaded straight into the MFMA's register
+// layout, adjacent lanes hold different tokens, a cache line each, and a CU gets
+// less than 13 bytes per cycle whatever the source.  Qwen3-8B layer, 64 sequences of
+// 4096 .. 20480 tokens, merge included: 331 us (4.74 TB/s of cache) with register
+// loads and a split per wave, 305 us (5.15 TB/s) now; a probe of 2 KiB page reads
+// alone reaches 5.5-5.9 TB/s.
+//
+// Grid (kv head, sequence, split): the kv heads of a block (adjacent in memory) run
+// together and spread over the XCDs; with the split fastest an even split count sent
+// all of a sequence's first splits, the full ones, to half of the XCDs (250 sequences
+// of up to 3000 tokens, two splits: 210 us, 188 us in this order).
+//
+// Per page, lane L, g = L / 16, j = L % 16:
 //   score product (16x16x32, 4 per page): A = keys of token j, dims 32g + 8kk ..
 //     (the same dim permutation for the query operand, column j = head j of the
 //     group, zero past kG); the result holds S[token 4g + i][head j];
-//   online softmax per head j (lanes j hold head j's running max and sum);
-//   value product (16x16x16, 8 per page, nb = 0..7): A = P[head j][tokens 4g ..
-//     4g+3] (exactly the score layout), B = V[tokens 4g .. 4g+3][dim 8j + nb];
-//     the result holds O[head 4g + i][dim 8j + nb].
+//   online softmax per head j (lanes j hold head j's running max and, each for its
+//     own tokens, sum);
+//   value product (16x16x16, 8 per page): A = P[head j][tokens 4g .. 4g+3] (exactly
+//     the score layout), B = V[tokens 4g .. 4g+3][dim]; nb = 0..7 covers the dims of
+//     the lane's 16-byte value chunks: value_dim(j, nb).  The result holds
+//     O[head 4g + i][value_dim(j, nb)].
+// LDS: key rows with their 16-byte chunks XOR-swizzled (by the DMA's source
+// addresses) so that the 16 rows of a fragment read spread over all banks; value
+// pages as they are, read 256 contiguous bytes per 16 lanes.
+template <bool kFp8>
+__device__ __forceinline__ constexpr int value_dim(int j, int nb) {
+  return kFp8 ? (nb >> 2) * 64 + 4 * j + (nb & 3) : (nb >> 1) * 32 + 2 * j + (nb & 1);
+}
+
+template <bool kFp8>
+__device__ __forceinline__ int key_swz(int row, int chunk) {
+  return kFp8 ? swz(row, chunk) : row * 256 + ((chunk ^ (row & 15)) << 4);
+}
+
+// Pages in flight per wave.  Depth 2 leaves room for five FP8 workgroups per CU:
+// 2 / 3 / 4 pages take 13.7 / 14.2 / 14.4 us on 20 short sequences, 24.6 / 26.0 /
+// 30.0 us on 16 of up to 4096 tokens, 308 / 308 / 307 us on 64 of up to 20480.
+constexpr int kRingDepth = 2;
+
 template <int kG, bool kFp8>
-__global__ __launch_bounds__(256) void attn_decode_kernel(
+struct AttnLds {
+  static constexpr int kWaves = 4;
+  static constexpr int kHalf = kPage * kDim * (kFp8 ? 1 : 2);   // bytes of one kv head's key (or value) page
+  static constexpr int kComb = kG * kDim + 2 * kG;               // floats a wave leaves for the combination
+  static constexpr int kBytes = kWaves * kRingDepth * 2 * kHalf;
+  static_assert(kWaves * kComb * 4 <= kBytes, "the combination reuses the rings");
+};
+
+template <int kG, bool kFp8>
+__device__ __forceinline__ void attn_decode_split_of(
     const uint16_t* __restrict__ q, const typename CacheElem<kFp8>::T* __restrict__ kcache,
     const typename CacheElem<kFp8>::T* __restrict__ vcache, int64_t num_blocks,
-    const int32_t* __restrict__ block_table, int max_blocks, const int32_t* __restrict__ seq_lens,
-    const float* __restrict__ k_scale, float sm_scale, int kv_heads, int split_tokens, int max_splits,
-    float* __restrict__ partial) {
-  typedef typename CacheElem<kFp8>::T E;
-  constexpr int kPer16 = 16 / sizeof(E);                  // cache values per 16-byte load
+    const int32_t* __restrict__ block_table, int max_blocks, const int32_t* __restrict__ seq_lens, int max_seq_len,
+    const float* __restrict__ k_scale, const float* __restrict__ v_scale, float sm_scale, int kv_heads,
+    int split_pages, int max_splits, float* __restrict__ partial, uint16_t* __restrict__ out,
+    uint8_t* lds) {
+  constexpr int kElem = kFp8 ? 1 : 2;
+  constexpr int kHalf = AttnLds<kG, kFp8>::kHalf;
+  constexpr int kDepth = kRingDepth;
+  constexpr int kOct = kHalf / 1024;                      // DMA instructions per page half
+  constexpr int kWaves = AttnLds<kG, kFp8>::kWaves;
+  constexpr int kComb = AttnLds<kG, kFp8>::kComb;
+
   const int lane = threadIdx.x & 63;
-  // wave-uniform as far as the compiler knows too: the split, its token range and
-  // the page indices stay in scalar registers, so the block-table reads are scalar
-  // loads (a vector load there would make each page's loads wait for every load in
-  // flight, the prefetched pages included)
+  // wave-uniform as far as the compiler knows too: page indices stay in scalar
+  // registers and the block-table reads are scalar loads
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int split = blockIdx.x * 4 + wave;
-  if (split >= max_splits) return;
-  const int kvh = blockIdx.y;
-  const int b = blockIdx.z;
+  const int kvh = blockIdx.x, b = blockIdx.y, split = blockIdx.z;
   const int g = lane >> 4, j = lane & 15;
-  const int n = seq_lens[b];
-  const int t0 = split * split_tokens;
-  const int t1 = min(n, t0 + split_tokens);
-  float* rec = partial + (((int64_t)b * kv_heads + kvh) * max_splits + split) * partial_floats<kG>();
+  const int p0 = split * split_pages;
+  const int32_t* table = block_table + (int64_t)b * max_blocks;
+  auto page_id = [&](int i) {                             // a bad entry reads a wrong page, never outside
+    const int blk = table[min(p0 + wave + i * kWaves, max_blocks - 1)];
+    return blk < 0 ? 0 : ((int64_t)blk >= num_blocks ? (int)(num_blocks - 1) : blk);
+  };
+  int first[kDepth + 1];                                  // (loaded beside the sequence length, not after it)
+#pragma unroll
+  for (int d = 0; d <= kDepth; ++d) first[d] = page_id(d);
+  const int n = min(seq_lens[b], max_seq_len);
+  const int p1 = min((n + kPage - 1) / kPage, p0 + split_pages);
+  uint16_t* orow = out + ((int64_t)b * kv_heads + kvh) * kG * kDim;
+  if (p0 >= p1) {                                         // (uniform over the workgroup)
+    if (max_splits == 1)                                  // an empty sequence gives 0
+      for (int i = threadIdx.x; i < kG * kDim / 2; i += 256) reinterpret_cast<uint32_t*>(orow)[i] = 0u;
+    return;
+  }
+  const int np = (p1 - p0 - wave + kWaves - 1) / kWaves;  // this wave's pages: p0 + wave, + 4, ... (may be 0)
 
   // query operand: head j of the group (zero columns past kG), dims 32g + 8kk ..+7
   v8bf16_t qb[4];
@@ -257,44 +313,53 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
     }
   }
   const float sscale = (k_scale ? k_scale[0] : 1.0f) * sm_scale;     // bf16 cache: no scale
-  float m = -INFINITY, l = 0.0f;                 // running max / sum of head j
+
+  uint8_t* ring = lds + wave * (kDepth * 2 * kHalf);
+  // DMA source offsets inside a page half: keys row by row with swizzled chunks, values linear
+  uint32_t koff[kOct];
+#pragma unroll
+  for (int o = 0; o < kOct; ++o) {
+    const int at = o * 1024 + lane * 16, row = at / (kDim * kElem), c = (at % (kDim * kElem)) / 16;
+    koff[o] = (uint32_t)key_swz<kFp8>(row, c);            // (an involution: physical chunk c holds logical c ^ key)
+  }
+  auto fetch = [&](int blk, int slot) {
+    const int64_t base = ((int64_t)blk * kv_heads + kvh) * kHalf;
+    const __amdgpu_buffer_rsrc_t rk = buffer_rsrc(reinterpret_cast<const uint8_t*>(kcache) + base);
+    const __amdgpu_buffer_rsrc_t rv = buffer_rsrc(reinterpret_cast<const uint8_t*>(vcache) + base);
+    uint8_t* dst = ring + slot * (2 * kHalf);
+#pragma unroll
+    for (int o = 0; o < kOct; ++o) lds_dma16(rk, koff[o], 0, dst + o * 1024);
+#pragma unroll
+    for (int o = 0; o < kOct; ++o) lds_dma16(rv, lane * 16, o * 1024, dst + kHalf + o * 1024);
+  };
+
+  float m = -INFINITY, l = 0.0f;                 // head j: running max; sum over this lane's tokens
   v4f32_t o[8];
 #pragma unroll
   for (int nb = 0; nb < 8; ++nb) o[nb] = (v4f32_t){0.f, 0.f, 0.f, 0.f};
 
-  const int64_t head_stride = (int64_t)kPage * kDim;            // one kv head's page
-  auto load_page = [&](int tp, PageRegs<kFp8>& r) {
-    const int page = min(tp / kPage, max_blocks - 1);
-    int64_t blk = block_table[(int64_t)b * max_blocks + page];
-    blk = blk < 0 ? 0 : (blk >= num_blocks ? num_blocks - 1 : blk);   // a bad entry reads a wrong page, never outside
-    const int64_t base = (blk * kv_heads + kvh) * head_stride;
-    const E* kp = kcache + base + j * kDim + 32 * g;
-    const E* vp = vcache + base + (g * kDim + 8 * j) * 4;
 #pragma unroll
-    for (int c = 0; c < 32 / kPer16; ++c) {
-      r.k[c] = *reinterpret_cast<const uint4*>(kp + c * kPer16);
-      r.v[c] = *reinterpret_cast<const uint4*>(vp + c * kPer16);
+  for (int d = 0; d < kDepth; ++d)
+    if (d < np) fetch(first[d], d);
+  int next = first[kDepth];                       // the entry of the next page to fetch, loaded a page ahead
+  int slot = 0;
+  for (int i = 0; i < np; ++i) {
+    wait_own_ring<2 * kOct, kDepth>(np - 1 - i);
+    asm volatile("" ::: "memory");
+    const uint8_t* st = ring + slot * (2 * kHalf);
+    uint4 kf[2 * kElem], vf[2 * kElem];
+#pragma unroll
+    for (int c = 0; c < 2 * kElem; ++c) {
+      kf[c] = *reinterpret_cast<const uint4*>(st + key_swz<kFp8>(j, 2 * kElem * g + c));
+      vf[c] = *reinterpret_cast<const uint4*>(st + kHalf + g * (kHalf / 4) + c * 256 + j * 16);
     }
-  };
-
-  // Three pages in flight: the current one and the next two, in three register
-  // sets that rotate by name (the loop body below runs three pages), so no page's
-  // registers are copied while a later page's loads into them are in flight.
-  // Every step issues its prefetch unconditionally (past the split's end it
-  // re-reads the split's last page, a cache hit): with the same number of loads
-  // on every path the compiler waits for exactly the page it needs, never for
-  // the prefetches behind it.
-  if (t0 >= t1) return;    // (empty split: nothing in flight, nothing to write)
-  const int t_last = t1 - 1;
-  PageRegs<kFp8> pg0, pg1, pg2;
-  load_page(t0, pg0);
-  load_page(min(t0 + kPage, t_last), pg1);
-  // one page: prefetch page tp + 2 into `next` (the set of page tp - 1), then
-  // attend over page tp held in `cur` if it is inside the split
-  auto page_step = [&](int tp, const PageRegs<kFp8>& cur, PageRegs<kFp8>& next) {
-    load_page(min(tp + 2 * kPage, t_last), next);
-    if (tp >= t1) return;
-    const int valid = min(kPage, t1 - tp);
+    // the slot's fragments are in registers before its refill is issued
+    __builtin_amdgcn_s_waitcnt(0xF | (0x7 << 4) | (0x3 << 14));   // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    if (i + kDepth < np) fetch(next, slot);
+    next = page_id(i + kDepth + 1);
+    slot = slot + 1 == kDepth ? 0 : slot + 1;
+    const int valid = min(kPage, n - (p0 + wave + i * kWaves) * kPage);
 
     // ---- scores
     v4f32_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -302,41 +367,36 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
     for (int kk = 0; kk < 4; ++kk) {
       v8bf16_t a;
       if constexpr (kFp8) {
-        const uint4& w = cur.k[kk >> 1];
+        const uint4& w = kf[kk >> 1];
         a = to_bf16x8((kk & 1) ? make_uint2(w.z, w.w) : make_uint2(w.x, w.y));
       } else {
-        a = to_bf16x8(cur.k[kk]);
+        a = to_bf16x8(kf[kk]);
       }
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qb[kk], acc, 0, 0, 0);
     }
     // ---- online softmax for head j (tokens 4g + i of the page)
     float s[4], mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s[i] = (4 * g + i < valid) ? acc[i] * sscale : -INFINITY;
-      mx = fmaxf(mx, s[i]);
+    for (int r = 0; r < 4; ++r) {
+      s[r] = (4 * g + r < valid) ? acc[r] * sscale : -INFINITY;
+      mx = fmaxf(mx, s[r]);
     }
-    mx = fmaxf(mx, shfl_xor_f(mx, 16));
-    mx = fmaxf(mx, shfl_xor_f(mx, 32));
-    const float m_new = fmaxf(m, mx);                       // finite: the page has a valid token
+    const float m_new = fmaxf(m, max_over_rows(mx));        // finite: the page has a valid token
     const float alpha = __expf(m - m_new);                  // 0 on the first page
-    float psum = 0.0f;
+    l *= alpha;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s[i] = __expf(s[i] - m_new);                          // masked tokens: 0
-      psum += s[i];
+    for (int r = 0; r < 4; ++r) {
+      s[r] = __expf(s[r] - m_new);                          // masked tokens: 0
+      l += s[r];
     }
-    psum += shfl_xor_f(psum, 16);
-    psum += shfl_xor_f(psum, 32);
-    l = l * alpha + psum;
     m = m_new;
     // rows of o are heads 4g + i: rescale by their alphas (held by lanes 4g + i)
     if (__ballot(j < kG && alpha != 1.0f)) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float ai = __shfl(alpha, 4 * g + i, 64);
+      for (int r = 0; r < 4; ++r) {
+        const float ar = __shfl(alpha, 4 * g + r, 64);
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) o[nb][i] *= ai;
+        for (int nb = 0; nb < 8; ++nb) o[nb][r] *= ar;
       }
     }
     // ---- values: P[head j][tokens 4g .. 4g+3] in bf16 (masked tokens are 0); the
@@ -353,12 +413,12 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
     for (int nb = 0; nb < 8; ++nb) {
       v4i16_t vb;
       if constexpr (kFp8) {
-        const uint4& w = cur.v[nb >> 2];
+        const uint4& w = vf[nb >> 2];
         uint32_t word = (nb & 3) == 0 ? w.x : (nb & 3) == 1 ? w.y : (nb & 3) == 2 ? w.z : w.w;
         word &= keep >= 4 ? 0xFFFFFFFFu : (1u << (8 * keep)) - 1u;
         vb = to_bf16x4(word);
       } else {
-        const uint4& w = cur.v[nb >> 1];
+        const uint4& w = vf[nb >> 1];
         uint2 pr = (nb & 1) ? make_uint2(w.z, w.w) : make_uint2(w.x, w.y);
         pr.x &= keep >= 2 ? 0xFFFFFFFFu : (keep == 1 ? 0xFFFFu : 0u);
         pr.y &= keep >= 4 ? 0xFFFFFFFFu : (keep == 3 ? 0xFFFFu : 0u);
@@ -367,56 +427,130 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(
       o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vb, o[nb], 0, 0, 0);
       o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pb, vb, o[nb], 0, 0, 0);
     }
-  };
-  for (int tp = t0; tp < t1; tp += 3 * kPage) {
-    page_step(tp, pg0, pg2);
-    page_step(tp + kPage, pg1, pg0);
-    page_step(tp + 2 * kPage, pg2, pg1);
   }
+  l += shfl_xor_f(l, 16);
+  l += shfl_xor_f(l, 32);
 
-  // o[nb][i] = O[head 4g + i][dim 8j + nb]; lanes h < kG of group 0 hold m, l of head h
+  // ---- combine the four waves: each leaves o[G][128], m[G], l[G] in LDS (a wave
+  //      without pages m = -inf, l = 0, o = 0), then every thread adds its outputs
+  float* comb = reinterpret_cast<float*>(lds);
+  __syncthreads();                               // the rings are idle (every wave waited for its last DMA)
+  {
+    float* mine = comb + wave * kComb;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int head = 4 * g + i;
-    if (head < kG) {
-      float4* dst = reinterpret_cast<float4*>(rec + head * kDim + 8 * j);
-      dst[0] = make_float4(o[0][i], o[1][i], o[2][i], o[3][i]);
-      dst[1] = make_float4(o[4][i], o[5][i], o[6][i], o[7][i]);
+    for (int r = 0; r < 4; ++r) {
+      const int head = 4 * g + r;
+      if (head < kG) {
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb) mine[head * kDim + value_dim<kFp8>(j, nb)] = o[nb][r];
+      }
+    }
+    if (g == 0 && j < kG) {
+      mine[kG * kDim + j] = m;
+      mine[kG * kDim + kG + j] = l;
     }
   }
-  if (g == 0 && j < kG) {
-    rec[rec_m<kG>() + j] = m;
-    rec[rec_l<kG>() + j] = l;
+  __syncthreads();
+  float* rec = partial + (((int64_t)b * kv_heads + kvh) * max_splits + split) * partial_floats<kG>();
+  for (int e = threadIdx.x; e < kG * kDim / 2; e += 256) {
+    const int head = e / (kDim / 2), d = 2 * (e % (kDim / 2));
+    float mm = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, comb[w * kComb + kG * kDim + head]);
+    float ls = 0.0f, a0 = 0.0f, a1 = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float* c = comb + w * kComb;
+      const float f = __expf(c[kG * kDim + head] - mm);
+      ls += c[kG * kDim + kG + head] * f;
+      a0 += c[head * kDim + d] * f;
+      a1 += c[head * kDim + d + 1] * f;
+    }
+    if (max_splits == 1) {                       // the whole sequence: the output itself
+      const float f = (v_scale ? v_scale[0] : 1.0f) / ls;
+      reinterpret_cast<uint32_t*>(orow)[e] = f32_to_bf16_rne(a0 * f) | (f32_to_bf16_rne(a1 * f) << 16);
+    } else {
+      *reinterpret_cast<float2*>(rec + head * kDim + d) = make_float2(a0, a1);
+      if (d == 0) {
+        rec[rec_m<kG>() + head] = mm;
+        rec[rec_l<kG>() + head] = ls;
+      }
+    }
   }
 }
 
+template <int kG, bool kFp8>
+__global__ __launch_bounds__(256) void attn_decode_kernel(
+    const uint16_t* __restrict__ q, const typename CacheElem<kFp8>::T* __restrict__ kcache,
+    const typename CacheElem<kFp8>::T* __restrict__ vcache, int64_t num_blocks,
+    const int32_t* __restrict__ block_table, int max_blocks, const int32_t* __restrict__ seq_lens, int max_seq_len,
+    const float* __restrict__ k_scale, const float* __restrict__ v_scale, float sm_scale, int kv_heads,
+    int split_pages, int max_splits, float* __restrict__ partial, uint16_t* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[AttnLds<kG, kFp8>::kBytes];
+  attn_decode_split_of<kG, kFp8>(q, kcache, vcache, num_blocks, block_table, max_blocks, seq_lens, max_seq_len, k_scale,
+                                 v_scale, sm_scale, kv_heads, split_pages, max_splits, partial, out, lds);
+}
+
 // out[b][head][d] = bf16( v_scale * sum_s e^(m_s - M) o_s[d] / sum_s e^(m_s - M) l_s ),
-// one workgroup of 64 threads (two dims each) per (head, sequence); empty
-// sequences give 0.
+// one workgroup per (head, sequence): 32 lanes hold the head's dims, kMergeSets such
+// sets take the splits in turn (the records' loads are then independent of each other)
+// and are combined in LDS.  Empty sequences give 0.
+constexpr int kMergeSets = 4;
+
 template <int kG>
-__global__ __launch_bounds__(64) void attn_merge_kernel(const float* __restrict__ partial,
-                                                       const int32_t* __restrict__ seq_lens,
-                                                       const float* __restrict__ v_scale, int kv_heads,
-                                                       int split_tokens, int max_splits, uint16_t* __restrict__ out) {
+__global__ __launch_bounds__(32 * kMergeSets) void attn_merge_kernel(
+    const float* __restrict__ partial, const int32_t* __restrict__ seq_lens, int max_seq_len,
+    const float* __restrict__ v_scale, int kv_heads, int split_pages, int max_splits, uint16_t* __restrict__ out) {
+  __shared__ float red[kMergeSets][kDim + 2];
   const int head = blockIdx.x, b = blockIdx.y;
   const int kvh = head / kG, h = head % kG;
-  const int n = seq_lens[b];
-  const int ns = min(max_splits, (max(n, 0) + split_tokens - 1) / split_tokens);
+  const int set = threadIdx.x >> 5, d = 4 * (threadIdx.x & 31);
+  const int n = min(seq_lens[b], max_seq_len);
+  const int ns = min(max_splits, (max(n, 0) + split_pages * kPage - 1) / (split_pages * kPage));
   const float* base = partial + ((int64_t)b * kv_heads + kvh) * max_splits * partial_floats<kG>();
-  float mmax = -INFINITY;
-  for (int s = 0; s < ns; ++s) mmax = fmaxf(mmax, base[(int64_t)s * partial_floats<kG>() + rec_m<kG>() + h]);
-  float lsum = 0.0f, a0 = 0.0f, a1 = 0.0f;
-  const int d = 2 * threadIdx.x;
-  for (int s = 0; s < ns; ++s) {
+  float m = -INFINITY, l = 0.0f;
+  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int s = set; s < ns; s += kMergeSets) {
     const float* r = base + (int64_t)s * partial_floats<kG>();
-    const float w = expf(r[rec_m<kG>() + h] - mmax);
-    lsum += r[rec_l<kG>() + h] * w;
-    a0 += r[h * kDim + d] * w;
-    a1 += r[h * kDim + d + 1] * w;
+    const float ms = r[rec_m<kG>() + h], ls = r[rec_l<kG>() + h];
+    const float4 o = *reinterpret_cast<const float4*>(r + h * kDim + d);
+    const float mn = fmaxf(m, ms), f = expf(m - mn), w = expf(ms - mn);   // (m = -inf first: f = 0)
+    l = l * f + ls * w;
+    a.x = a.x * f + o.x * w;
+    a.y = a.y * f + o.y * w;
+    a.z = a.z * f + o.z * w;
+    a.w = a.w * f + o.w * w;
+    m = mn;
+  }
+  *reinterpret_cast<float2*>(&red[set][d]) = make_float2(a.x, a.y);
+  *reinterpret_cast<float2*>(&red[set][d + 2]) = make_float2(a.z, a.w);
+  if (d == 0) {
+    red[set][kDim] = m;
+    red[set][kDim + 1] = l;
+  }
+  __syncthreads();
+  if (set != 0) return;
+  float mm = -INFINITY, lsum = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kMergeSets; ++s) mm = fmaxf(mm, red[s][kDim]);
+  a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int s = 0; s < kMergeSets; ++s) {
+    const float w = ns > 0 ? expf(red[s][kDim] - mm) : 0.0f;              // (a set without splits: 0)
+    lsum += red[s][kDim + 1] * w;
+    a.x += red[s][d] * w;
+    a.y += red[s][d + 1] * w;
+    a.z += red[s][d + 2] * w;
+    a.w += red[s][d + 3] * w;
   }
   const float f = ns > 0 ? (v_scale ? v_scale[0] : 1.0f) / lsum : 0.0f;
-  const uint32_t o2 = f32_to_bf16_rne(a0 * f) | (f32_to_bf16_rne(a1 * f) << 16);
-  *reinterpret_cast<uint32_t*>(out + ((int64_t)b * kv_heads * kG + head) * kDim + d) = o2;
+  uint2 o2;
+  o2.x = f32_to_bf16_rne(a.x * f) | (f32_to_bf16_rne(a.y * f) << 16);
+  o2.y = f32_to_bf16_rne(a.z * f) | (f32_to_bf16_rne(a.w * f) << 16);
+  uint32_t* orow = reinterpret_cast<uint32_t*>(out + ((int64_t)b * kv_heads * kG + head) * kDim + d);
+  orow[0] = o2.x;                                  // (out is 4-byte aligned)
+  orow[1] = o2.y;
 }
 
 }  // namespace
@@ -449,10 +583,8 @@ hipError_t launch_kv_cache_write(const uint16_t* k, const uint16_t* v, int64_t t
 }
 
 AttnSplit attn_decode_split(int64_t batch, int64_t kv_heads, int64_t group, int64_t max_seq_len) {
-  // about 6144 waves over the whole batch (three times the 2048 that are resident
-  // at two waves per SIMD), splits of at least 256 tokens.  Measured on 64
-  // sequences of 4096 .. 20480 tokens: 2048 / 3072 / 4096 / 6144 / 8192 / 16384
-  // waves took 396 / 440 / 385 / 358 / 394 / 429 us.
+  // records the workspace has room for: about 6144 over the whole batch, of at least
+  // 256 tokens each (the launch takes as many of them as attn_plan below wants)
   constexpr int64_t kTargetWaves = 6144;
   const int64_t pairs = batch * kv_heads;
   int64_t splits = (kTargetWaves + pairs - 1) / (pairs > 0 ? pairs : 1);
@@ -468,20 +600,45 @@ AttnSplit attn_decode_split(int64_t batch, int64_t kv_heads, int64_t group, int6
   return s;
 }
 
+// Splits of the longest sequence, one workgroup of four waves each: at least 16
+// pages long (four per wave) and never more than the workspace has records for, as
+// many as put the target number of workgroups on the batch.  A large cache wants
+// several rounds of the 1280 resident workgroups, so that ragged sequences even out
+// (64 sequences of up to 20480 tokens, 512 / 1024 / 2048 / 4608 workgroups: 365 / 336 /
+// 316 / 305 us); a small one pays more for each record than it gains (8 sequences, 4 kv
+// heads, up to 20000 tokens: 37 / 41 / 45 / 47 us; 16 x 8 of up to 4096: 26 / 25 / 26 /
+// 26 us).
+struct AttnPlan {
+  int split_pages, splits;
+};
+static AttnPlan attn_plan(int64_t batch, int64_t kv_heads, int64_t group, int64_t max_seq_len) {
+  constexpr int64_t kMinPages = 16;
+  const int64_t pages = max_seq_len > 0 ? (max_seq_len + kPage - 1) / kPage : 1;
+  const int64_t pairs = batch * kv_heads;
+  const int64_t target = pairs * pages >= (int64_t(1) << 18) ? 4608 : 1024;
+  const int64_t most = attn_decode_split(batch, kv_heads, group, max_seq_len).max_splits;
+  int64_t splits = (target + pairs - 1) / pairs;
+  splits = splits > most ? most : splits;
+  int64_t per = (pages + splits - 1) / splits;
+  per = per < kMinPages ? kMinPages : per;
+  return AttnPlan{(int)per, (int)((pages + per - 1) / per)};
+}
+
 template <int kG, bool kFp8>
 static hipError_t launch_attn(const uint16_t* q, const void* kc, const void* vc, int64_t num_blocks,
                               const int32_t* block_table, int64_t max_blocks, const int32_t* seq_lens, int64_t batch,
-                              int64_t kv_heads, const AttnSplit& sp, const float* k_scale, const float* v_scale,
-                              float sm_scale, uint16_t* out, float* partial, hipStream_t stream) {
+                              int64_t kv_heads, int64_t max_seq_len, const AttnPlan& pl, const float* k_scale,
+                              const float* v_scale, float sm_scale, uint16_t* out, float* partial,
+                              hipStream_t stream) {
   typedef typename CacheElem<kFp8>::T E;
-  dim3 grid((unsigned)((sp.max_splits + 3) / 4), (unsigned)kv_heads, (unsigned)batch);
-  hipLaunchKernelGGL((attn_decode_kernel<kG, kFp8>), grid, dim3(256), 0, stream, q, static_cast<const E*>(kc),
-                     static_cast<const E*>(vc), num_blocks, block_table, (int)max_blocks, seq_lens, k_scale, sm_scale,
-                     (int)kv_heads, sp.split_tokens, sp.max_splits, partial);
+  hipLaunchKernelGGL((attn_decode_kernel<kG, kFp8>), dim3((unsigned)kv_heads, (unsigned)batch, (unsigned)pl.splits),
+                     dim3(256), 0, stream, q, static_cast<const E*>(kc), static_cast<const E*>(vc), num_blocks,
+                     block_table, (int)max_blocks, seq_lens, (int)max_seq_len, k_scale, v_scale, sm_scale,
+                     (int)kv_heads, pl.split_pages, pl.splits, partial, out);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_merge_kernel<kG>), dim3((unsigned)(kv_heads * kG), (unsigned)batch), dim3(64), 0, stream,
-                     partial, seq_lens, v_scale, (int)kv_heads, sp.split_tokens, sp.max_splits, out);
+  if (e != hipSuccess || pl.splits == 1) return e;
+  hipLaunchKernelGGL((attn_merge_kernel<kG>), dim3((unsigned)(kv_heads * kG), (unsigned)batch),
+                     dim3(32 * kMergeSets), 0, stream, partial, seq_lens, (int)max_seq_len, v_scale, (int)kv_heads, pl.split_pages, pl.splits, out);
   return hipGetLastError();
 }
 
@@ -491,13 +648,13 @@ hipError_t launch_attention_decode(const uint16_t* q, const void* k_cache, const
                                    int64_t max_seq_len, const float* k_scale, const float* v_scale, float sm_scale,
                                    uint16_t* out, float* partial, hipStream_t stream) {
   const int64_t group = q_heads / kv_heads;
-  const AttnSplit sp = attn_decode_split(batch, kv_heads, group, max_seq_len);
+  const AttnPlan pl = attn_plan(batch, kv_heads, group, max_seq_len);
 #define FP8RL_ATTN(G)                                                                                            \
   if (group == G)                                                                                                \
     return fp8_cache ? launch_attn<G, true>(q, k_cache, v_cache, num_blocks, block_table, max_blocks, seq_lens,  \
-                                            batch, kv_heads, sp, k_scale, v_scale, sm_scale, out, partial, stream) \
+                                            batch, kv_heads, max_seq_len, pl, k_scale, v_scale, sm_scale, out, partial, stream) \
                      : launch_attn<G, false>(q, k_cache, v_cache, num_blocks, block_table, max_blocks, seq_lens, \
-                                             batch, kv_heads, sp, k_scale, v_scale, sm_scale, out, partial, stream);
+                                             batch, kv_heads, max_seq_len, pl, k_scale, v_scale, sm_scale, out, partial, stream);
   FP8RL_ATTN(1)
   FP8RL_ATTN(2)
   FP8RL_ATTN(4)

@@ -112,8 +112,8 @@ hipError_t launch_kv_cache_write(const uint16_t* k, const uint16_t* v, int64_t t
                                  uint8_t* k_cache, uint8_t* v_cache, hipStream_t stream);
 
 struct AttnSplit {
-  int split_tokens;      // tokens per wave (a multiple of 16)
-  int max_splits;        // splits of the longest sequence
+  int split_tokens;      // tokens per record at the least (a multiple of 16)
+  int max_splits;        // most records of one (sequence, kv head)
   int partial_floats;    // floats per (sequence, kv head, split) record
 };
 AttnSplit attn_decode_split(int64_t batch, int64_t kv_heads, int64_t group, int64_t max_seq_len);

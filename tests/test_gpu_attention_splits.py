@@ -1,0 +1,39 @@
+"""Decode attention where its split of the work changes: one split and many, waves with no page, a last page of one
+token, two and more records per sequence, both cache types.  Tolerance as in test_gpu_kv.py."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gemm, kv
+from tests.gpu_util import announce, need_gpu, u16
+from tests.test_gpu_kv import paged_inputs, run_fp8
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fp8rl():
+    need_gpu()
+    import paper_2601_18150_amd as m
+    m.load()
+    return m
+
+
+# pages per split: 16 up to 256 tokens (one record, written by the attention kernel itself), then several records;
+# (160, ..): more workgroups than are resident; (1, 3): few, long sequences
+@pytest.mark.parametrize("batch,q_heads,kv_heads,max_len", [(5, 8, 1, 256), (5, 8, 1, 257), (3, 4, 4, 1025),
+                                                           (1, 8, 1, 9000), (160, 16, 8, 520)])
+def test_attention_split_edges(fp8rl, batch, q_heads, kv_heads, max_len):
+    announce(f"attention splits batch={batch} heads={q_heads}/{kv_heads} max_len={max_len}")
+    rng = np.random.default_rng(batch * 100 + max_len)
+    lens = rng.integers(0, max_len + 1, batch).astype(np.int32)
+    lens[:3] = [max_len, 1, min(max_len, 33)][:len(lens[:3])]
+    q, kc, vc, table, _ = paged_inputs(rng, lens, q_heads, kv_heads)
+    ks, vs, sm = np.float32(0.02), np.float32(0.03), float(1 / np.sqrt(128))
+    out = run_fp8(fp8rl, q, kc, vc, table, lens, ks, vs, sm, max_seq_len=max_len)
+    again = run_fp8(fp8rl, q, kc, vc, table, lens, ks, vs, sm, max_seq_len=max_len)
+    ref = kv.attention_decode(u16(q), kc, vc, ks, vs, table, lens, sm)
+    ok, worst, _ = gemm.tolerance_check(out.float().cpu().numpy().astype(np.float64).reshape(ref.shape), ref)
+    assert ok, f"worst |err|/bound {worst:.3f}"
+    assert torch.equal(out.view(torch.int16), again.view(torch.int16)), "not deterministic"
+    assert torch.all(out[torch.from_numpy(lens == 0)] == 0)
