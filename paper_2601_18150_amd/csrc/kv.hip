@@ -62,87 +62,136 @@ __global__ __launch_bounds__(256) void amax_partial_kernel(const uint16_t* __res
   if (threadIdx.x == 0) partial[blockIdx.x] = max(max(red[0], red[1]), max(red[2], red[3]));
 }
 
-__global__ __launch_bounds__(64) void scale_final_kernel(const uint32_t* __restrict__ partial, int blocks,
+// At most kMaxAmaxBlocks maxima, four loads in flight per thread (64 threads walking
+// them sixteen deep took 4.6 us; a launch that does nothing takes about 2.5).
+constexpr int kMaxAmaxBlocks = 1024;
+
+__global__ __launch_bounds__(256) void scale_final_kernel(const uint32_t* __restrict__ partial, int blocks,
                                                         float* __restrict__ scale) {
-  uint32_t m = 0;
-  for (int b = threadIdx.x; b < blocks; b += 64) m = max(m, partial[b]);
+  __shared__ uint32_t red[4];
+  uint32_t v[kMaxAmaxBlocks / 256];
+#pragma unroll
+  for (int i = 0; i < kMaxAmaxBlocks / 256; ++i) v[i] = partial[min((int)threadIdx.x + 256 * i, blocks - 1)];
+  uint32_t m = v[0];
+#pragma unroll
+  for (int i = 1; i < kMaxAmaxBlocks / 256; ++i) m = max(m, v[i]);
   m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = max(max(red[0], red[1]), max(red[2], red[3]));
   if (threadIdx.x == 0) scale[0] = m == 0u ? 1.0f : __uint_as_float(m << 16) / kE4M3Max;   // IEEE division
 }
 
 // ---------------------------------------------------------------------------
-// Cache write: one thread per (four consecutive tokens, kv head, 8-dim chunk)
-// of K and V.  code = E4M3(fl32(x / s)) saturated at +-448 (IEEE division; the
-// sign of x is OR-ed back so that -0 gives 0x80).  Slots outside
-// [0, num_blocks * 16) are skipped (negative slots mark padding tokens).
-// When the four tokens go to four consecutive slots starting at a multiple of 4
-// (a prefill's tokens, in order), their value codes fill whole dwords of the
-// value page (dim d: tokens 4a .. 4a+3) and are stored as 32 contiguous bytes;
-// otherwise each token's value codes are stored byte by byte.
+// Cache write: one thread per (kTok consecutive tokens, kv head, 8-dim chunk) of K
+// and V.  code = E4M3(fl32(x / s)) saturated at +-448 (the sign of x is OR-ed back
+// so that -0 gives 0x80).  Slots outside [0, num_blocks * 16) are skipped (negative
+// slots mark padding tokens).
+// Four tokens per thread: when they go to four consecutive slots starting at a
+// multiple of 4 (a prefill's tokens, in order), their value codes fill whole dwords
+// of the value page (dim d: tokens 4a .. 4a+3) and are stored as 32 contiguous
+// bytes; otherwise each token's value codes are stored byte by byte.  One token per
+// thread for small calls (decode steps), which are one chain of latencies.  Graph
+// replay, four tokens / one token per thread (in brackets four with an IEEE division
+// per element and loads behind the slots): 64 scattered tokens x 8 heads 7.4 / 3.5 us
+// [8.7], 500 in order 4.2 / 4.0 [5.5], 2000 in order 5.0 / 8.9 [6.5], 13500 in order 16.3 /
+// 42.4 [20.9].
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t quant4_static(uint32_t w0, uint32_t w1, float s) {
+// fl32(x / s) to within what decides its E4M3 code: Markstein's correction of
+// x * fl32(1 / s) is the correctly rounded quotient while no intermediate leaves the
+// normal range (quant_math.hpp).  For s in [2^-91, 2^110] that holds from quotients
+// of 2^-11 (the smaller ones all give code 0) up to the clamp of the first estimate
+// at 1024, beyond which the result stays above 448 and saturates.  Any other s
+// divides.
+struct StaticScale {
+  float s, r;
+  bool fast;
+};
+
+__device__ __forceinline__ StaticScale static_scale(float s) {
+  return StaticScale{s, 1.0f / s, s >= 0x1p-91f && s <= 0x1p110f};
+}
+
+template <bool kFast>
+__device__ __forceinline__ float static_quotient(float x, const StaticScale& sc) {
+  if (!kFast) return x / sc.s;
+  const float q0 = fminf(fmaxf(x * sc.r, -1024.0f), 1024.0f);
+  return __builtin_fmaf(__builtin_fmaf(-q0, sc.s, x), sc.r, q0);
+}
+
+template <bool kFast>
+__device__ __forceinline__ uint32_t quant4_static(uint32_t w0, uint32_t w1, const StaticScale& sc) {
   float q[4] = {__uint_as_float(w0 << 16), __uint_as_float(w0 & 0xFFFF0000u), __uint_as_float(w1 << 16),
                 __uint_as_float(w1 & 0xFFFF0000u)};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) q[i] = fminf(fmaxf(q[i] / s, -kE4M3Max), kE4M3Max);
+  for (int i = 0; i < 4; ++i) q[i] = fminf(fmaxf(static_quotient<kFast>(q[i], sc), -kE4M3Max), kE4M3Max);
   int c = __builtin_amdgcn_cvt_pk_fp8_f32(q[0], q[1], 0, false);
   c = __builtin_amdgcn_cvt_pk_fp8_f32(q[2], q[3], c, true);
   const uint32_t signs = __builtin_amdgcn_perm(w1, w0, 0x07050301u) & 0x80808080u;
   return (uint32_t)c | signs;
 }
 
-// byte j of the result = byte `b` of word j (4x4 byte transpose, one output word)
-__device__ __forceinline__ uint32_t gather_byte(const uint32_t (&w)[4], int b) {
-  return ((w[0] >> (8 * b)) & 0xFFu) | (((w[1] >> (8 * b)) & 0xFFu) << 8) | (((w[2] >> (8 * b)) & 0xFFu) << 16) |
-         (((w[3] >> (8 * b)) & 0xFFu) << 24);
+__device__ __forceinline__ uint2 quant8_static(const uint4& v, const StaticScale& sc) {
+  return sc.fast ? make_uint2(quant4_static<true>(v.x, v.y, sc), quant4_static<true>(v.z, v.w, sc))
+                 : make_uint2(quant4_static<false>(v.x, v.y, sc), quant4_static<false>(v.z, v.w, sc));
 }
 
+// byte j of the result = byte `b` of word j (4x4 byte transpose, one output word)
+__device__ __forceinline__ uint32_t gather_byte(const uint32_t (&w)[4], int b) {
+  const uint32_t pick = 0x0C0C0400u + 0x0101u * (uint32_t)b;          // (0x0C: a zero byte)
+  return __builtin_amdgcn_perm(w[1], w[0], pick) | __builtin_amdgcn_perm(w[3], w[2], pick) << 16;
+}
+
+template <int kTok>
 __global__ __launch_bounds__(256) void kv_write_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                       int64_t tokens, int kv_heads, const int64_t* __restrict__ slots,
                                                       int64_t num_blocks, const float* __restrict__ k_scale,
                                                       const float* __restrict__ v_scale, uint8_t* __restrict__ kc,
                                                       uint8_t* __restrict__ vc) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t per_quad = (int64_t)kv_heads * (kDim / 8);
-  const int64_t quads = (tokens + 3) / 4;
-  if (i >= quads * per_quad) return;
-  const int64_t tq = i / per_quad;
-  const int rem = (int)(i - tq * per_quad);
-  const int h = rem / (kDim / 8), c = rem % (kDim / 8);
-  const int64_t t0 = tq * 4;
-  const int nt = (int)min((int64_t)4, tokens - t0);
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;      // below 2^31 (checked by the caller)
+  const uint32_t per = (uint32_t)kv_heads * (kDim / 8);
+  const uint32_t tq = i / per, rem = i - tq * per;
+  const int h = (int)(rem / (kDim / 8)), c = (int)(rem % (kDim / 8));
+  const int64_t t0 = (int64_t)tq * kTok;
+  if (t0 >= tokens) return;
+  const int nt = (int)min((int64_t)kTok, tokens - t0);
   const int64_t limit = num_blocks * kPage;
-  const float sk = k_scale[0], sv = v_scale[0];
-  int64_t slot[4];
-  uint32_t vlo[4] = {0u, 0u, 0u, 0u}, vhi[4] = {0u, 0u, 0u, 0u};   // value codes of dims c*8 .. +3, +4 .. +7
+  // every load in flight before any is used (tokens past the end re-read the last)
+  int64_t slot[kTok];
+  uint4 xk[kTok], xv[kTok];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    slot[r] = r < nt ? slots[t0 + r] : -1;
-    if (r < nt) {
-      const int64_t src = ((t0 + r) * kv_heads + h) * kDim + c * 8;
-      const uint4 xk = *reinterpret_cast<const uint4*>(k + src);
-      const uint4 xv = *reinterpret_cast<const uint4*>(v + src);
-      vlo[r] = quant4_static(xv.x, xv.y, sv);
-      vhi[r] = quant4_static(xv.z, xv.w, sv);
-      if (slot[r] >= 0 && slot[r] < limit) {
-        const int64_t blk = slot[r] / kPage, off = slot[r] % kPage;
-        *reinterpret_cast<uint2*>(kc + ((blk * kv_heads + h) * kPage + off) * kDim + c * 8) =
-            make_uint2(quant4_static(xk.x, xk.y, sk), quant4_static(xk.z, xk.w, sk));
-      }
+  for (int r = 0; r < kTok; ++r) {
+    const int64_t t = t0 + min(r, nt - 1), src = (t * kv_heads + h) * kDim + c * 8;
+    slot[r] = slots[t];
+    xk[r] = *reinterpret_cast<const uint4*>(k + src);
+    xv[r] = *reinterpret_cast<const uint4*>(v + src);
+  }
+  const StaticScale sk = static_scale(k_scale[0]), sv = static_scale(v_scale[0]);
+  uint32_t vlo[kTok], vhi[kTok];                           // value codes of dims c*8 .. +3, +4 .. +7
+#pragma unroll
+  for (int r = 0; r < kTok; ++r) {
+    const uint2 ck = quant8_static(xk[r], sk), cv = quant8_static(xv[r], sv);
+    vlo[r] = cv.x;
+    vhi[r] = cv.y;
+    if (r < nt && slot[r] >= 0 && slot[r] < limit) {
+      const int64_t blk = slot[r] / kPage, off = slot[r] % kPage;
+      *reinterpret_cast<uint2*>(kc + ((blk * kv_heads + h) * kPage + off) * kDim + c * 8) = ck;
     }
   }
-  const bool packed = nt == 4 && slot[0] >= 0 && slot[0] + 3 < limit && (slot[0] & 3) == 0 &&
-                      slot[1] == slot[0] + 1 && slot[2] == slot[0] + 2 && slot[3] == slot[0] + 3;
-  if (packed) {
-    // dword of dim d = the four tokens' codes of d, dims c*8 .. c*8+7 contiguous
-    const int64_t blk = slot[0] / kPage, off = slot[0] % kPage;
-    uint4* vd = reinterpret_cast<uint4*>(vc + ((blk * kv_heads + h) * kPage * kDim) + ((off >> 2) * kDim + c * 8) * 4);
-    vd[0] = make_uint4(gather_byte(vlo, 0), gather_byte(vlo, 1), gather_byte(vlo, 2), gather_byte(vlo, 3));
-    vd[1] = make_uint4(gather_byte(vhi, 0), gather_byte(vhi, 1), gather_byte(vhi, 2), gather_byte(vhi, 3));
-    return;
+  if constexpr (kTok == 4) {
+    const bool packed = nt == 4 && slot[0] >= 0 && slot[0] + 3 < limit && (slot[0] & 3) == 0 &&
+                        slot[1] == slot[0] + 1 && slot[2] == slot[0] + 2 && slot[3] == slot[0] + 3;
+    if (packed) {
+      // dword of dim d = the four tokens' codes of d, dims c*8 .. c*8+7 contiguous
+      const int64_t blk = slot[0] / kPage, off = slot[0] % kPage;
+      uint4* vd = reinterpret_cast<uint4*>(vc + ((blk * kv_heads + h) * kPage * kDim) + ((off >> 2) * kDim + c * 8) * 4);
+      vd[0] = make_uint4(gather_byte(vlo, 0), gather_byte(vlo, 1), gather_byte(vlo, 2), gather_byte(vlo, 3));
+      vd[1] = make_uint4(gather_byte(vhi, 0), gather_byte(vhi, 1), gather_byte(vhi, 2), gather_byte(vhi, 3));
+      return;
+    }
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
+  for (int r = 0; r < kTok; ++r) {
     if (r >= nt || slot[r] < 0 || slot[r] >= limit) continue;
     // values: byte (off / 4, dim, off % 4) of the page
     const int64_t blk = slot[r] / kPage, off = slot[r] % kPage;
@@ -560,7 +609,7 @@ __global__ __launch_bounds__(32 * kMergeSets) void attn_merge_kernel(
 // ---------------------------------------------------------------------------
 int kv_amax_blocks(int64_t n) {
   const int64_t b = (n / 8 + 255) / 256;
-  return (int)(b < 1 ? 1 : (b > 1024 ? 1024 : b));
+  return (int)(b < 1 ? 1 : (b > kMaxAmaxBlocks ? kMaxAmaxBlocks : b));
 }
 
 hipError_t launch_kv_calibrate_scale(const uint16_t* x, int64_t n, float* scale, uint32_t* partial,
@@ -569,16 +618,25 @@ hipError_t launch_kv_calibrate_scale(const uint16_t* x, int64_t n, float* scale,
   hipLaunchKernelGGL(amax_partial_kernel, dim3(blocks), dim3(256), 0, stream, x, n, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(scale_final_kernel, dim3(1), dim3(64), 0, stream, partial, blocks, scale);
+  hipLaunchKernelGGL(scale_final_kernel, dim3(1), dim3(256), 0, stream, partial, blocks, scale);
   return hipGetLastError();
 }
+
+// (token, kv head) pairs up to which a cache write runs one token per thread.
+constexpr int64_t kSmallWrite = 4096;
 
 hipError_t launch_kv_cache_write(const uint16_t* k, const uint16_t* v, int64_t tokens, int kv_heads,
                                  const int64_t* slots, int64_t num_blocks, const float* k_scale, const float* v_scale,
                                  uint8_t* k_cache, uint8_t* v_cache, hipStream_t stream) {
-  const int64_t threads = (tokens + 3) / 4 * kv_heads * (kDim / 8);
-  hipLaunchKernelGGL(kv_write_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, k, v, tokens,
-                     kv_heads, slots, num_blocks, k_scale, v_scale, k_cache, v_cache);
+  const auto blocks = [&](int64_t per_thread) {
+    return (unsigned)(((tokens + per_thread - 1) / per_thread * kv_heads * (kDim / 8) + 255) / 256);
+  };
+  if (tokens * kv_heads <= kSmallWrite)
+    hipLaunchKernelGGL(kv_write_kernel<1>, dim3(blocks(1)), dim3(256), 0, stream, k, v, tokens, kv_heads, slots,
+                       num_blocks, k_scale, v_scale, k_cache, v_cache);
+  else
+    hipLaunchKernelGGL(kv_write_kernel<4>, dim3(blocks(4)), dim3(256), 0, stream, k, v, tokens, kv_heads, slots,
+                       num_blocks, k_scale, v_scale, k_cache, v_cache);
   return hipGetLastError();
 }
 
