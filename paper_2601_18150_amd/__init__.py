@@ -123,29 +123,30 @@ def _check(name: str, status: int):
 
 
 def _stream(stream=None) -> int:
+    # (the raw handle of the current device's current stream: torch.cuda.current_stream() builds a Stream
+    # object each time, 3 us of a small call's 12)
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
 
 
 def _dev(*ts):
-    dev = None
+    dev = ts[0].get_device()
     for t in ts:
         if not t.is_cuda:
             raise ValueError("fp8rl tensors must live on a HIP device")
-        if dev is None:
-            dev = t.device
-        elif t.device != dev:
+        if t.get_device() != dev:
             raise ValueError("fp8rl tensors must share one device")
-    return dev
 
 
 def _ld(t: torch.Tensor) -> int:
-    if t.dim() != 2 or t.stride(1) != 1:
+    st = t.stride()
+    if len(st) != 2 or st[1] != 1:
         raise ValueError("expected a 2-D row-major tensor with unit column stride")
-    return t.stride(0) if t.size(0) > 1 else max(t.stride(0), t.size(1))
+    rows, cols = t.shape
+    return st[0] if rows > 1 else max(st[0], cols)
 
 
 def _u8(t: torch.Tensor) -> torch.Tensor:
@@ -277,13 +278,14 @@ def _dense_args(qa, sa, qw, sw, y):
         raise ValueError("K mismatch")
     if sa.dtype != torch.float32 or sw.dtype != torch.float32:
         raise TypeError("scales must be fp32")
-    if sa.dim() != 2 or sa.size(0) != k // 128 or sa.stride(1) != 1 or sa.size(1) < m:
+    sa_shape = sa.shape
+    if len(sa_shape) != 2 or sa_shape[0] != k // 128 or sa.stride(1) != 1 or sa_shape[1] < m:
         raise ValueError("sa must be [K/128][ld >= M] with unit stride")
     if not sw.is_contiguous() or sw.numel() != (n // 128) * (k // 128):
         raise ValueError("sw must be contiguous [N/128][K/128]")
     if y is None:
         y = torch.empty((m, n), dtype=torch.bfloat16, device=qa.device)
-    if y.dtype != torch.bfloat16 or tuple(y.shape) != (m, n):
+    elif y.dtype != torch.bfloat16 or y.shape != (m, n):
         raise ValueError("y must be bf16 [M][N]")
     _dev(qa, sa, qw, sw, y)
     return qa, qw, y, m, n, k
@@ -633,5 +635,6 @@ gather_rows_fp8 = fp8rl_gather_rows_fp8
 def linear_w8a8(x: torch.Tensor, qw: torch.Tensor, sw: torch.Tensor, stream=None) -> torch.Tensor:
     """The W8A8 linear layer's forward: dynamic activation quantisation, then the
     blockwise FP8 GEMM, both on one stream with no host synchronisation."""
+    stream = _stream(stream)
     qa, sa = fp8rl_quant_act_token_group128(x, stream=stream)
     return fp8rl_gemm_w8a8_block(qa, sa, qw, sw, stream=stream)
