@@ -6,6 +6,14 @@
 
 namespace fp8rl {
 
+// Launch bounds of every kernel with MFMA, also those launched with 256 threads:
+// where a lane could have more than 256 registers, the compiler puts each MFMA
+// result into the same four accumulation registers and copies it out
+// (v_accvgpr_read, four per MFMA, each MFMA waiting for the copies of the one
+// before); with room for 512 threads it has to stay within 256 and uses vector
+// registers throughout (777 tokens through the Qwen3-8B MLP, 128x128 tiles: 225 -> 207 us).
+constexpr int kMfmaBounds = 512;
+
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // Per-half unsigned max of two packed u16 pairs (v_pk_max_u16).

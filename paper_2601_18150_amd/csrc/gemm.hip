@@ -110,7 +110,7 @@ struct OneJob {
 
 // kMx: power-of-two scales through the MX-scaled MFMA (gemm_core.hpp).
 template <class C, bool kMx>
-__global__ __launch_bounds__(C::kThreads) void gemm_w8a8_block_kernel(
+__global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_kernel(
     const uint8_t* __restrict__ qa, int64_t lda, const float* __restrict__ sa, int64_t ld_sa,
     const uint8_t* __restrict__ qw, int64_t ldw, const float* __restrict__ sw,
     uint16_t* __restrict__ y, int64_t ldy, int64_t M, int64_t N, int KB, int tiles_m, int tiles_n) {
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(C::kThreads) void gemm_w8a8_block_kernel(
 // renumbered as in the dense kernel, split slowest, so the tiles an XCD runs
 // together share their weight rows.
 template <class C>
-__global__ __launch_bounds__(C::kThreads) void gemm_w8a8_block_splitk_kernel(
+__global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_splitk_kernel(
     const uint8_t* __restrict__ qa, int64_t lda, const float* __restrict__ sa, int64_t ld_sa,
     const uint8_t* __restrict__ qw, int64_t ldw, const float* __restrict__ sw,
     float* __restrict__ part, int64_t M, int64_t N, int KB, int tiles_m, int tiles_n, int splits) {
@@ -224,7 +224,7 @@ struct GroupedJobs {
 // kGather: output row r takes its activation row from source row gidx[r] of qa
 // ([src_rows][lda]) and sa ([K/128][ld_sa]); otherwise qa is [rows][K].
 template <class C, bool kMx, bool kGather>
-__global__ __launch_bounds__(C::kThreads) void grouped_gemm_w8a8_block_kernel(
+__global__ __launch_bounds__(kMfmaBounds) void grouped_gemm_w8a8_block_kernel(
     const uint8_t* __restrict__ qa, const float* __restrict__ sa, int64_t ld_sa,
     const uint8_t* __restrict__ qw, const float* __restrict__ sw,
     const int32_t* __restrict__ offsets, int G, uint16_t* __restrict__ y, int64_t N, int64_t K, int tiles_n,

@@ -157,13 +157,12 @@ __device__ __forceinline__ void wait_vmcnt() {
 // must be an immediate, hence the branches (later <= S - 2).
 template <int S, int kPer>
 __device__ __forceinline__ void wait_dma_step(int later) {
-  static_assert(S >= 2 && S <= 4, "ring depth 2..4");
-  if constexpr (S == 2) {
-    wait_vmcnt<0>();
-  } else if constexpr (S == 3) {
-    if (later >= 1) wait_vmcnt<kPer>(); else wait_vmcnt<0>();
+  static_assert(S >= 2 && (S - 2) * kPer < 64, "vmcnt is 6 bits");
+  if constexpr (S > 2) {
+    if (later >= S - 2) { wait_vmcnt<(S - 2) * kPer>(); return; }
+    wait_dma_step<S - 1, kPer>(later);
   } else {
-    if (later >= 2) wait_vmcnt<2 * kPer>(); else if (later == 1) wait_vmcnt<kPer>(); else wait_vmcnt<0>();
+    wait_vmcnt<0>();
   }
 }
 

@@ -172,7 +172,7 @@ __device__ __forceinline__ void small_tile(const uint8_t* __restrict__ wbase, ui
 
 // Dense, m <= 8 * AO: workgroup b owns weight rows b * kRows ..
 template <class C, bool kMx>
-__global__ __launch_bounds__(C::kThreads) void gemm_small_kernel(
+__global__ __launch_bounds__(kMfmaBounds) void gemm_small_kernel(
     const uint8_t* __restrict__ qa, int64_t lda, const float* __restrict__ sa, int64_t ld_sa,
     const uint8_t* __restrict__ qw, int64_t ldw, const float* __restrict__ sw, uint16_t* __restrict__ y, int64_t ldy,
     int m, int KB) {
@@ -203,7 +203,7 @@ struct GroupedSmall {
 };
 
 template <int WK, bool kMx, bool kGather>
-__global__ __launch_bounds__(256) void grouped_gemm_small_kernel(
+__global__ __launch_bounds__(kMfmaBounds) void grouped_gemm_small_kernel(
     const uint8_t* __restrict__ qa, int64_t lda, const float* __restrict__ sa, int64_t ld_sa,
     const uint8_t* __restrict__ qw, const float* __restrict__ sw, const int32_t* __restrict__ offsets,
     uint16_t* __restrict__ y, int64_t N, int64_t K, const int32_t* __restrict__ gidx, int src_rows) {

@@ -529,7 +529,7 @@ __device__ __forceinline__ void attn_decode_split_of(
 }
 
 template <int kG, bool kFp8>
-__global__ __launch_bounds__(256) void attn_decode_kernel(
+__global__ __launch_bounds__(kMfmaBounds) void attn_decode_kernel(
     const uint16_t* __restrict__ q, const typename CacheElem<kFp8>::T* __restrict__ kcache,
     const typename CacheElem<kFp8>::T* __restrict__ vcache, int64_t num_blocks,
     const int32_t* __restrict__ block_table, int max_blocks, const int32_t* __restrict__ seq_lens, int max_seq_len,
