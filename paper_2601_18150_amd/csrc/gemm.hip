@@ -7,31 +7,47 @@
 #include <atomic>
 
 #include "gemm_core.hpp"
+#include "gemm_pipe.hpp"
 #include "launch.hpp"
 
 namespace fp8rl {
 namespace {
 
-// Tile configurations (BN x BM, waves, LDS ring depth), measured on MI355X:
-// - M and N >= 2048: 256x256, 8 waves, 2 slots (one workgroup per CU).
-// - other M > 256, and the grouped GEMM with K > 1024: 128x128, 4 waves, 2
-//   slots: two workgroups per CU walking their tiles as one pipeline.  Deeper
-//   rings with one tile per workgroup were slower (MoE gate_up 270 vs 205 us).
-// - the grouped GEMM with K <= 1024: 256n x 128m, 8 waves, 2 slots, one
-//   workgroup per CU walking its tiles as one pipeline: half as many tiles, so
-//   short K loops pay fewer tile ends (Qwen3-30B-A3B down, K = 768: 104-106 vs
-//   118-120 us; gate_up, K = 2048, is 2-4% slower with it).
-// - 128 < M <= 256 (decode batches): 64x64 tiles, 4 waves, 3 slots, one tile per
-//   workgroup, when they number at most 512 (Qwen3-8B at M = 256: qkv 21.6 vs
-//   24.0 us, o_proj 17.0 vs 21.3 us for split-K 128x128 tiles); otherwise one
-//   256-token tile, 128x256, 8 waves, 3 slots (gate_up: 44 vs 48 us for 128x128,
-//   59 us for 64x64).
-// - split-K ranges: 128x128, 3 slots (decode linears 123 vs 129 us per layer).
+// Tile configurations: BN x BM, waves along n and m, LDS ring depth.
+//
+// Dense products are one round or several of tiles over the 256 CUs, and a tile's
+// time is its K blocks times a step time that hardly depends on the shape; so the
+// tile is the one with the smallest (rounds x step time), tile_for() below.  Step
+// times (us per 128-wide K block and round, Qwen3-8B linears, 80 .. 2000 tokens,
+// weights from HBM; about 3 us per call besides):
+//   64x64      0.32   gemm_pipe, two wave groups split K
+//   64x128, 128x64  0.49   the same
+//   128x128    0.66   gemm_pipe, eight waves, 4-slot ring
+//   128x256, 256x128  1.2 (1.07 with few bytes of weights)  gemm_pipe, 3-slot ring
+//   256x256    1.5 in one round, 1.75 a round in several (2.05 at 8192 tokens, where
+//              the power limit lowers the clock)   gemm_tiles
+//   128x128, two workgroups per CU walking their tiles as one pipeline (gemm_tiles):
+//              1.25 per 512 tiles, 0.75 for a last half
+// Against the three fixed ranges of rows that chose the tile before (us): M = 300
+// qkv 32.2 -> 17.9, o_proj 31.4 -> 15.8, gate_up 68.9 -> 53.8, down 87 -> 38.8; M = 777
+// o_proj 31.4 -> 23.2, down 86.3 -> 60.5; M = 2000 qkv 64.8 -> 53.4, gate_up 228.7 ->
+// 183.8; M = 256 o_proj 15.9 -> 13.2, qkv 21.2 -> 18.6.
 using CfgLarge = GemmCfg<256, 256, 2, 4, 2>;   // 512 threads, wave tile 128(n) x 64(m), 130 KiB LDS
 using CfgSmall = GemmCfg<128, 128, 2, 2, 2>;   // 256 threads, wave tile 64 x 64, 65 KiB LDS
-using CfgDecode = GemmCfg<128, 256, 2, 4, 3>;  // 512 threads, wave tile 64 x 64, 147 KiB LDS
-using CfgDecodeNarrow = GemmCfg<64, 64, 2, 2, 3>;   // 256 threads, wave tile 32 x 32, 49 KiB LDS
-using CfgSplitK = GemmCfg<128, 128, 2, 2, 3>;  // one tile per workgroup, 2 K steps in flight, 98 KiB LDS
+using Cfg64x64 = GemmCfg<64, 64, 2, 2, 4>;     // two groups: 512 threads, wave tile 32 x 32, 130 KiB LDS
+using Cfg64x128 = GemmCfg<64, 128, 2, 2, 3>;   // two groups: 512 threads, wave tile 32 x 64, 147 KiB LDS
+using Cfg128x64 = GemmCfg<128, 64, 2, 2, 3>;   // two groups: 512 threads, wave tile 64 x 32, 146 KiB LDS
+using Cfg128x128 = GemmCfg<128, 128, 2, 4, 4>; // 512 threads, wave tile 64 x 32, 130 KiB LDS
+using Cfg128x256 = GemmCfg<128, 256, 2, 4, 3>; // 512 threads, wave tile 64 x 64, 147 KiB LDS
+using Cfg256x128 = GemmCfg<256, 128, 4, 2, 3>; // 512 threads, wave tile 64 x 64, 146 KiB LDS
+// Split-K ranges: one tile per workgroup, 2 K steps in flight (2 / 3 / 4 slots: decode
+// linears 129 / 123 / 125 us per layer).
+using CfgSplitK = GemmCfg<128, 128, 2, 2, 3>;
+// The grouped GEMM with K > 1024: 128x128, two persistent workgroups per CU (deeper rings
+// with one tile per workgroup were slower: MoE gate_up 270 vs 205 us); with K <= 1024
+// 256n x 128m, one persistent workgroup per CU: half as many tiles, so short K loops
+// pay fewer tile ends (Qwen3-30B-A3B down, K = 768: 104-106 vs 118-120 us; gate_up,
+// K = 2048, is 2-4% slower with it).
 using CfgGroupedShortK = GemmCfg<256, 128, 4, 2, 2>;   // 512 threads, wave tile 64 x 64, 97 KiB LDS
 using CfgGrouped = CfgSmall;
 
@@ -118,6 +134,17 @@ __global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_kernel(
   DenseJobs<C> jobs{(int)blockIdx.x, (int)gridDim.x, tiles_m, tiles_n, (int)M};
   gemm_tiles<C, false, kCrossTiles<C>, DenseJobs<C>, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, KB, y, ldy, nullptr,
                                                           (int)N, KB, jobs, lds);
+}
+
+// One tile per workgroup of C::kThreads * WK threads (gemm_pipe.hpp).
+template <class C, int WK, bool kMx>
+__global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_pipe_kernel(
+    const uint8_t* __restrict__ qa, int64_t lda, const float* __restrict__ sa, int64_t ld_sa,
+    const uint8_t* __restrict__ qw, int64_t ldw, const float* __restrict__ sw,
+    uint16_t* __restrict__ y, int64_t ldy, int64_t M, int64_t N, int KB, int tiles_m, int tiles_n) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kPipeLds<C, WK>];
+  DenseJobs<C> jobs{(int)blockIdx.x, (int)gridDim.x, tiles_m, tiles_n, (int)M};
+  gemm_pipe<C, WK, DenseJobs<C>, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, KB, y, ldy, (int)N, KB, jobs, lds);
 }
 
 // Split-K dense GEMM, for shapes whose tiles alone cannot fill the GPU (decode:
@@ -304,27 +331,86 @@ hipError_t launch_grouped(const uint8_t* qa, const float* sa, int64_t ld_sa, con
 
 }  // namespace
 
-// Decode batches (128 < M <= 256) whose 64x64 tiles number at most 512 (two per CU).
-static bool decode_narrow_tiles(int64_t m, int64_t n) { return ((m + 63) / 64) * (n / 64) <= 512; }
+namespace {
+
+// Dense tile configurations in the order that breaks ties.
+enum class Tile { k64x64, k64x128, k128x64, k128x128, k128x256, k256x128, k256x256, kPersistent };
+
+struct TileChoice {
+  Tile tile;
+  double step;      // rounds x step time, us per K block
+};
+
+// The smallest rounds x step time (figures at the configurations above).
+TileChoice tile_for(int64_t m, int64_t n) {
+  struct Cost {
+    Tile tile;
+    int bn, bm;
+    double one, more;      // us per K block: a single round, each of several
+  };
+  static constexpr Cost kCosts[] = {
+      {Tile::k64x64, 64, 64, 0.32, 0.32},     {Tile::k64x128, 64, 128, 0.49, 0.49},
+      {Tile::k128x64, 128, 64, 0.49, 0.49},   {Tile::k128x128, 128, 128, 0.66, 0.66},
+      {Tile::k128x256, 128, 256, 1.2, 1.2},   {Tile::k256x128, 256, 128, 1.2, 1.2},
+      {Tile::k256x256, 256, 256, 1.5, 1.75},
+  };
+  const int64_t pairs = ((m + 127) / 128) * (n / 128) / 512, rest = ((m + 127) / 128) * (n / 128) % 512;
+  TileChoice best{Tile::kPersistent, 1.25 * (double)pairs + (rest == 0 ? 0.0 : rest <= 256 ? 0.9 : 1.25)};
+  if (pairs > 0 && rest > 0 && rest <= 256) best.step -= 0.15;
+  for (const Cost& c : kCosts) {
+    const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
+    const int64_t rounds = (tiles + kCus - 1) / kCus;
+    const double step = rounds == 1 ? c.one : c.more * (double)rounds;
+    if (step < best.step) best = {c.tile, step};
+  }
+  return best;
+}
+
+template <class C, int WK, bool kMx>
+hipError_t launch_pipe(const uint8_t* qa, int64_t lda, const float* sa, int64_t ld_sa, const uint8_t* qw, int64_t ldw,
+                       const float* sw, uint16_t* y, int64_t ldy, int64_t m, int64_t n, int64_t k,
+                       hipStream_t stream) {
+  const int tiles_m = (int)((m + C::BM - 1) / C::BM);
+  const int tiles_n = (int)((n + C::BN - 1) / C::BN);
+  hipLaunchKernelGGL((gemm_w8a8_block_pipe_kernel<C, WK, kMx>), dim3((unsigned)((int64_t)tiles_m * tiles_n)),
+                     dim3(C::kThreads * WK), 0, stream, qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, (int)(k / 128),
+                     tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
+template <bool kMx>
+hipError_t launch_tile(Tile tile, const uint8_t* qa, int64_t lda, const float* sa, int64_t ld_sa, const uint8_t* qw,
+                       int64_t ldw, const float* sw, uint16_t* y, int64_t ldy, int64_t m, int64_t n, int64_t k,
+                       hipStream_t stream) {
+#define FP8RL_PIPE(C, WK) return launch_pipe<C, WK, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
+  switch (tile) {
+    case Tile::k64x64: FP8RL_PIPE(Cfg64x64, 2);
+    case Tile::k64x128: FP8RL_PIPE(Cfg64x128, 2);
+    case Tile::k128x64: FP8RL_PIPE(Cfg128x64, 2);
+    case Tile::k128x128: FP8RL_PIPE(Cfg128x128, 1);
+    case Tile::k128x256: FP8RL_PIPE(Cfg128x256, 1);
+    case Tile::k256x128: FP8RL_PIPE(Cfg256x128, 1);
+    case Tile::k256x256: return launch_dense<CfgLarge, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream);
+    case Tile::kPersistent: break;
+  }
+#undef FP8RL_PIPE
+  return launch_dense<CfgSmall, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream);
+}
+
+}  // namespace
 
 hipError_t launch_gemm_w8a8_block(const uint8_t* qa, int64_t lda, const float* sa, int64_t ld_sa,
                                   const uint8_t* qw, int64_t ldw, const float* sw, uint16_t* y, int64_t ldy,
                                   int64_t m, int64_t n, int64_t k, hipStream_t stream, bool pow2_scales) {
   if (m <= kSmallTokens && n < kSmallMaxN)
     return launch_gemm_small(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream, pow2_scales);
-  const bool large = m >= 2048 && n >= 2048;
-  const bool decode = !large && m > 128 && m <= 256;
-  const bool narrow = decode && decode_narrow_tiles(m, n);
-  if (pow2_scales)
-    return large    ? launch_dense<CfgLarge, true>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
-           : narrow ? launch_dense<CfgDecodeNarrow, true>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
-           : decode ? launch_dense<CfgDecode, true>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
-                    : launch_dense<CfgSmall, true>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream);
-  return large    ? launch_dense<CfgLarge, false>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
-         : narrow ? launch_dense<CfgDecodeNarrow, false>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
-         : decode ? launch_dense<CfgDecode, false>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
-                  : launch_dense<CfgSmall, false>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream);
+  const Tile tile = tile_for(m, n).tile;
+  return pow2_scales ? launch_tile<true>(tile, qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
+                     : launch_tile<false>(tile, qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream);
 }
+
+// Decode batches (128 < M <= 256) whose 64x64 tiles number at most 512 (two per CU).
+static bool decode_narrow_tiles(int64_t m, int64_t n) { return ((m + 63) / 64) * (n / 64) <= 512; }
 
 int splitk_factor(int64_t m, int64_t n, int64_t k) {
   // Split K only when the 128x128 tiles cover less than half of MI355X's 256
@@ -350,9 +436,15 @@ hipError_t launch_gemm_w8a8_block_splitk(const uint8_t* qa, int64_t lda, const f
                                          const uint8_t* qw, int64_t ldw, const float* sw, uint16_t* y,
                                          int64_t ldy, int64_t m, int64_t n, int64_t k, float* part, int splits,
                                          hipStream_t stream) {
-  // few tokens need no K ranges across workgroups (measured at M = 64, down: 20.6 us
-  // against 20.2 us split with its reduction; every other shape faster)
-  if (m <= kSmallTokens && n < kSmallMaxN) return launch_gemm_small(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream, false);
+  // Few tokens need no K ranges across workgroups (measured at M = 64, down: 20.6 us
+  // against 20.2 us split with its reduction; every other shape faster), and others
+  // only where their ranges, the partial sums (16 MiB: 9 us) and the second launch beat
+  // the unsplit tile.  Split / unsplit us: M = 128 down 22.9 / 34, M = 256 down 29.6 /
+  // 34; M = 128 qkv 18.7 / 13.5, o_proj 20.5 / 13.1, M = 300 o_proj 23.1 / 15.8, down
+  // 42.4 / 38.8.
+  const double kb = (double)(k / 128), mib = (double)(splits * m * n) / (1 << 18);
+  if ((m <= kSmallTokens && n < kSmallMaxN) || tile_for(m, n).step * kb <= 0.75 * kb / splits + 9.0 * mib / 16.0)
+    return launch_gemm_w8a8_block(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream, false);
   using C = CfgSplitK;
   const int tiles_m = (int)((m + C::BM - 1) / C::BM);
   const int tiles_n = (int)(n / C::BN);

@@ -1,0 +1,49 @@
+"""The dense GEMM across its tile choices (64x64 to 256x256, one tile per workgroup and persistent): ragged last
+tiles in both directions, fewer K blocks than ring slots or wave groups, odd K block counts, padded operands.  Pass
+criterion per element as in test_gpu_gemm.py."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gemm
+from tests.gpu_util import announce, need_gpu
+from tests.test_gpu_gemm_small import close, operands, padded, pow2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fp8rl():
+    need_gpu()
+    import paper_2601_18150_amd as m
+    m.load()
+    return m
+
+
+@pytest.mark.parametrize("m,n,k", [
+    (65, 128, 128), (100, 256, 384), (129, 1024, 13 * 128), (256, 4096, 9 * 128),      # 64x64, two K groups
+    (300, 4096, 128), (512, 4096, 5 * 128),                                             # 64x128
+    (300, 6144, 256), (257, 5120, 7 * 128),                                             # 128x64
+    (777, 4096, 128), (1000, 4096, 6 * 128),                                            # 128x128, eight waves
+    (200, 24576, 384), (777, 6272, 4 * 128),                                            # 128x256
+    (640, 24704, 128), (600, 24576, 5 * 128),                                           # 256x128, last tile of 128
+    (1300, 6272, 128), (300, 24704, 384),                                               # 256x256, last tile of 128
+    (1400, 12800, 256),                                                                 # persistent 128x128
+])
+def test_dense_tile_choices(fp8rl, m, n, k):
+    announce(f"gemm tiles m={m} n={n} k={k}")
+    qa, sa, qw, sw = operands(np.random.default_rng(m + n + k), m, n, k)
+    q, s, w = padded(qa, 48, torch.uint8)[:, :k], padded(sa[:, :m], 5, torch.float32), padded(qw, 16, torch.uint8)[:, :k]
+    sw_d = torch.from_numpy(sw).cuda()
+    out = torch.full((m + 1, n + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+    fp8rl.fp8rl_gemm_w8a8_block(q, s, w, sw_d, y=out[:m, :n])
+    again = fp8rl.fp8rl_gemm_w8a8_block(q, s, w, sw_d)
+    torch.cuda.synchronize()
+    close(out[:m, :n], gemm.gemm_ref_fp64(qa, sa, qw, sw), "fp32 scales")
+    assert torch.equal(again.view(torch.int16), out[:m, :n].contiguous().view(torch.int16)), "not deterministic"
+    assert torch.all(out[m:] == 7.0) and torch.all(out[:, n:] == 7.0), "wrote outside y"
+    if m * n * k < 2e9:
+        p_a, p_w = pow2(sa), pow2(sw)
+        y2 = fp8rl.fp8rl_gemm_w8a8_block_ue8m0(q, padded(p_a[:, :m], 5, torch.float32), w, torch.from_numpy(p_w).cuda())
+        torch.cuda.synchronize()
+        close(y2, gemm.gemm_ref_fp64(qa, p_a, qw, p_w), "power-of-two scales")
