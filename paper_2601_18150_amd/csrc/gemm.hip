@@ -43,12 +43,10 @@ using Cfg256x128 = GemmCfg<256, 128, 4, 2, 3>; // 512 threads, wave tile 64 x 64
 // Split-K ranges: one tile per workgroup, 2 K steps in flight (2 / 3 / 4 slots: decode
 // linears 129 / 123 / 125 us per layer).
 using CfgSplitK = GemmCfg<128, 128, 2, 2, 3>;
-// The grouped GEMM with K > 1024: 128x128, two persistent workgroups per CU (deeper rings
-// with one tile per workgroup were slower: MoE gate_up 270 vs 205 us); with K <= 1024
-// 256n x 128m, one persistent workgroup per CU: half as many tiles, so short K loops
-// pay fewer tile ends (Qwen3-30B-A3B down, K = 768: 104-106 vs 118-120 us; gate_up,
-// K = 2048, is 2-4% slower with it).
-using CfgGroupedShortK = GemmCfg<256, 128, 4, 2, 2>;   // 512 threads, wave tile 64 x 64, 97 KiB LDS
+// The grouped GEMM: 128x128, two persistent workgroups per CU (gate_up of the expert
+// block, 4096 tokens: 177 us; 256n x 128m 197, 128n x 64m 216, gemm_pipe with one
+// workgroup per CU walking 256n x 128m / 128x128 tiles 196 / 212; down, K = 768: 108
+// us, 256n x 128m 117, 128n x 64m 133).
 using CfgGrouped = CfgSmall;
 
 constexpr int kXcds = 8;        // MI355X: workgroup i is dispatched to XCD i % 8
@@ -494,16 +492,11 @@ hipError_t launch_grouped_gemm_w8a8_block(const uint8_t* qa, const float* sa, in
   if (total_rows <= kSmallRowsPerExpert * num_groups && n < kSmallMaxN)
     return launch_grouped_small(qa, k, sa, ld_sa, qw, sw, group_offsets, num_groups, total_rows, y, n, k, nullptr, 0,
                                 stream, pow2_scales);
-  const bool short_k = k <= 1024;
   if (pow2_scales)
-    return short_k ? launch_grouped<CfgGroupedShortK, true>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups,
-                                                             total_rows, y, n, k, stream)
-                   : launch_grouped<CfgGrouped, true>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups, total_rows,
-                                                      y, n, k, stream);
-  return short_k ? launch_grouped<CfgGroupedShortK, false>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups,
-                                                            total_rows, y, n, k, stream)
-                 : launch_grouped<CfgGrouped, false>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups, total_rows, y,
-                                                     n, k, stream);
+    return launch_grouped<CfgGrouped, true>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups, total_rows, y, n, k,
+                                            stream);
+  return launch_grouped<CfgGrouped, false>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups, total_rows, y, n, k,
+                                           stream);
 }
 
 hipError_t launch_grouped_gemm_w8a8_block_gathered(const uint8_t* qa, int64_t lda, const float* sa, int64_t ld_sa,
@@ -514,9 +507,6 @@ hipError_t launch_grouped_gemm_w8a8_block_gathered(const uint8_t* qa, int64_t ld
   if (total_rows <= kSmallRowsPerExpert * num_groups && n < kSmallMaxN)
     return launch_grouped_small(qa, lda, sa, ld_sa, qw, sw, group_offsets, num_groups, total_rows, y, n, k, row_index,
                                 src_rows, stream, false);
-  if (k <= 1024)
-    return launch_grouped<CfgGroupedShortK, false, true>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups,
-                                                         total_rows, y, n, k, stream, row_index, src_rows, lda);
   return launch_grouped<CfgGrouped, false, true>(qa, sa, ld_sa, qw, sw, group_offsets, num_groups, total_rows, y,
                                                  n, k, stream, row_index, src_rows, lda);
 }
