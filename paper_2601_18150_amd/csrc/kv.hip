@@ -83,19 +83,20 @@ __global__ __launch_bounds__(256) void scale_final_kernel(const uint32_t* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Cache write: one thread per (kTok consecutive tokens, kv head, 8-dim chunk) of K
-// and V.  code = E4M3(fl32(x / s)) saturated at +-448 (the sign of x is OR-ed back
-// so that -0 gives 0x80).  Slots outside [0, num_blocks * 16) are skipped (negative
-// slots mark padding tokens).
-// Four tokens per thread: when they go to four consecutive slots starting at a
-// multiple of 4 (a prefill's tokens, in order), their value codes fill whole dwords
-// of the value page (dim d: tokens 4a .. 4a+3) and are stored as 32 contiguous
-// bytes; otherwise each token's value codes are stored byte by byte.  One token per
-// thread for small calls (decode steps), which are one chain of latencies.  Graph
-// replay, four tokens / one token per thread (in brackets four with an IEEE division
-// per element and loads behind the slots): 64 scattered tokens x 8 heads 7.4 / 3.5 us
-// [8.7], 500 in order 4.2 / 4.0 [5.5], 2000 in order 5.0 / 8.9 [6.5], 13500 in order 16.3 /
-// 42.4 [20.9].
+// Cache write: code = E4M3(fl32(x / s)) saturated at +-448 (the sign of x is OR-ed
+// back so that -0 gives 0x80).  Slots outside [0, num_blocks * 16) are skipped
+// (negative slots mark padding tokens).  A thread handles 8 dims of one kv head's
+// keys and values.
+// The value page holds four slots 4a .. 4a+3 of a dim in one dword, so a group is up
+// to four tokens in a row whose slots follow each other inside one such dword: four of
+// them are stored as 32 contiguous bytes, fewer byte by byte.  kv_write_kernel: a
+// thread looks at the groups that start inside four consecutive tokens, one of them
+// where a prompt's tokens lie in order, wherever in the batch the prompt starts.
+// kv_write_token_kernel: one token per thread, for small calls (decode steps), which
+// are one chain of latencies.  Graph replay, us, at first (four tokens per thread and
+// position in the call, an IEEE division per element, loads behind the slots) / now: 64
+// scattered tokens x 8 heads 8.7 / 3.6, 500 in order 5.5 / 4.1, 13500 in order 20.0 / 16.5,
+// the same from slot 3 on (no four tokens of one dword at a multiple of four) 46.7 / 16.8.
 // ---------------------------------------------------------------------------
 // fl32(x / s) to within what decides its E4M3 code: Markstein's correction of
 // x * fl32(1 / s) is the correctly rounded quotient while no intermediate leaves the
@@ -142,66 +143,122 @@ __device__ __forceinline__ uint32_t gather_byte(const uint32_t (&w)[4], int b) {
   return __builtin_amdgcn_perm(w[1], w[0], pick) | __builtin_amdgcn_perm(w[3], w[2], pick) << 16;
 }
 
-template <int kTok>
-__global__ __launch_bounds__(256) void kv_write_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                                                      int64_t tokens, int kv_heads, const int64_t* __restrict__ slots,
-                                                      int64_t num_blocks, const float* __restrict__ k_scale,
-                                                      const float* __restrict__ v_scale, uint8_t* __restrict__ kc,
-                                                      uint8_t* __restrict__ vc) {
-  const uint32_t i = blockIdx.x * 256u + threadIdx.x;      // below 2^31 (checked by the caller)
-  const uint32_t per = (uint32_t)kv_heads * (kDim / 8);
-  const uint32_t tq = i / per, rem = i - tq * per;
-  const int h = (int)(rem / (kDim / 8)), c = (int)(rem % (kDim / 8));
-  const int64_t t0 = (int64_t)tq * kTok;
-  if (t0 >= tokens) return;
-  const int nt = (int)min((int64_t)kTok, tokens - t0);
-  const int64_t limit = num_blocks * kPage;
-  // every load in flight before any is used (tokens past the end re-read the last)
-  int64_t slot[kTok];
-  uint4 xk[kTok], xv[kTok];
+struct KvWrite {
+  const uint16_t* k;
+  const uint16_t* v;
+  uint8_t* kc;
+  uint8_t* vc;
+  int kv_heads;
+};
+
+// One token's value codes (dims c * 8 ..) to its slot, byte by byte.
+__device__ __forceinline__ void kv_store_value_bytes(const KvWrite& p, int64_t slot, int h, int c, const uint2& codes) {
+  const int off = (int)(slot % kPage);
+  uint8_t* vd = p.vc + (slot / kPage * p.kv_heads + h) * (kPage * kDim) + ((off >> 2) * kDim + c * 8) * 4 + (off & 3);
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    vd[4 * d] = (uint8_t)(codes.x >> (8 * d));
+    vd[4 * (d + 4)] = (uint8_t)(codes.y >> (8 * d));
+  }
+}
+
+__device__ __forceinline__ void kv_store_key(const KvWrite& p, int64_t slot, int h, int c, const uint2& codes) {
+  *reinterpret_cast<uint2*>(p.kc + (slot / kPage * p.kv_heads + h) * (kPage * kDim) + (slot % kPage) * kDim + c * 8) =
+      codes;
+}
+
+// kTok tokens from t, kv head h, dims c * 8 .., to slot[0 ..] (kRun: the first nt of
+// them, to consecutive slots inside one dword of the value page).
+template <int kTok, bool kRun>
+__device__ __forceinline__ void kv_write_tokens(const KvWrite& p, int64_t t, int nt, const int64_t (&slot)[kTok], int h,
+                                                int c, const StaticScale& sk, const StaticScale& sv) {
+  uint4 xk[kTok], xv[kTok];                                // every load in flight before any is used
 #pragma unroll
   for (int r = 0; r < kTok; ++r) {
-    const int64_t t = t0 + min(r, nt - 1), src = (t * kv_heads + h) * kDim + c * 8;
-    slot[r] = slots[t];
-    xk[r] = *reinterpret_cast<const uint4*>(k + src);
-    xv[r] = *reinterpret_cast<const uint4*>(v + src);
+    const int64_t src = ((t + (kRun ? min(r, nt - 1) : r)) * p.kv_heads + h) * kDim + c * 8;
+    xk[r] = *reinterpret_cast<const uint4*>(p.k + src);
+    xv[r] = *reinterpret_cast<const uint4*>(p.v + src);
   }
-  const StaticScale sk = static_scale(k_scale[0]), sv = static_scale(v_scale[0]);
   uint32_t vlo[kTok], vhi[kTok];                           // value codes of dims c*8 .. +3, +4 .. +7
 #pragma unroll
   for (int r = 0; r < kTok; ++r) {
-    const uint2 ck = quant8_static(xk[r], sk), cv = quant8_static(xv[r], sv);
+    const uint2 cv = quant8_static(xv[r], sv);
     vlo[r] = cv.x;
     vhi[r] = cv.y;
-    if (r < nt && slot[r] >= 0 && slot[r] < limit) {
-      const int64_t blk = slot[r] / kPage, off = slot[r] % kPage;
-      *reinterpret_cast<uint2*>(kc + ((blk * kv_heads + h) * kPage + off) * kDim + c * 8) = ck;
-    }
+    if (!kRun || r < nt) kv_store_key(p, kRun ? slot[0] + r : slot[r], h, c, quant8_static(xk[r], sk));
   }
-  if constexpr (kTok == 4) {
-    const bool packed = nt == 4 && slot[0] >= 0 && slot[0] + 3 < limit && (slot[0] & 3) == 0 &&
-                        slot[1] == slot[0] + 1 && slot[2] == slot[0] + 2 && slot[3] == slot[0] + 3;
-    if (packed) {
-      // dword of dim d = the four tokens' codes of d, dims c*8 .. c*8+7 contiguous
-      const int64_t blk = slot[0] / kPage, off = slot[0] % kPage;
-      uint4* vd = reinterpret_cast<uint4*>(vc + ((blk * kv_heads + h) * kPage * kDim) + ((off >> 2) * kDim + c * 8) * 4);
-      vd[0] = make_uint4(gather_byte(vlo, 0), gather_byte(vlo, 1), gather_byte(vlo, 2), gather_byte(vlo, 3));
-      vd[1] = make_uint4(gather_byte(vhi, 0), gather_byte(vhi, 1), gather_byte(vhi, 2), gather_byte(vhi, 3));
-      return;
+  if (kRun && nt == kTok) {
+    // dword of dim d = the four tokens' codes of d, dims c*8 .. c*8+7 contiguous
+    if constexpr (kTok == 4) {
+      const int off = (int)(slot[0] % kPage);
+      uint4* vq = reinterpret_cast<uint4*>(p.vc + (slot[0] / kPage * p.kv_heads + h) * (kPage * kDim) +
+                                           ((off >> 2) * kDim + c * 8) * 4);
+      vq[0] = make_uint4(gather_byte(vlo, 0), gather_byte(vlo, 1), gather_byte(vlo, 2), gather_byte(vlo, 3));
+      vq[1] = make_uint4(gather_byte(vhi, 0), gather_byte(vhi, 1), gather_byte(vhi, 2), gather_byte(vhi, 3));
     }
+    return;
   }
 #pragma unroll
-  for (int r = 0; r < kTok; ++r) {
-    if (r >= nt || slot[r] < 0 || slot[r] >= limit) continue;
-    // values: byte (off / 4, dim, off % 4) of the page
-    const int64_t blk = slot[r] / kPage, off = slot[r] % kPage;
-    uint8_t* vd = vc + (blk * kv_heads + h) * kPage * kDim + ((off >> 2) * kDim + c * 8) * 4 + (off & 3);
+  for (int r = 0; r < kTok; ++r)
+    if (!kRun || r < nt) kv_store_value_bytes(p, kRun ? slot[0] + r : slot[r], h, c, make_uint2(vlo[r], vhi[r]));
+}
+
+__global__ __launch_bounds__(256) void kv_write_kernel(const KvWrite p, int64_t tokens,
+                                                      const int64_t* __restrict__ slots, int64_t num_blocks,
+                                                      const float* __restrict__ k_scale,
+                                                      const float* __restrict__ v_scale) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;      // below 2^31 (checked by the caller)
+  const uint32_t per = (uint32_t)p.kv_heads * (kDim / 8);
+  const uint32_t tq = i / per, rem = i - tq * per;
+  const int h = (int)(rem / (kDim / 8)), c = (int)(rem % (kDim / 8));
+  const int64_t t0 = (int64_t)tq * 4;
+  if (t0 >= tokens) return;
+  const int64_t limit = num_blocks * kPage;
+  const StaticScale sk = static_scale(k_scale[0]), sv = static_scale(v_scale[0]);
+  // slots of tokens t0 - 1 .. t0 + 6 (outside the call: -2, which follows nothing)
+  int64_t s[8];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      vd[4 * d] = (uint8_t)(vlo[r] >> (8 * d));
-      vd[4 * (d + 4)] = (uint8_t)(vhi[r] >> (8 * d));
-    }
+  for (int j = 0; j < 8; ++j) {
+    const int64_t t = t0 - 1 + j;
+    s[j] = t >= 0 && t < tokens ? slots[t] : -2;
   }
+  // groups that start at t0 .. t0 + 3: their lengths, 4 bits each (0: none)
+  uint32_t lens = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t a = s[r + 1];
+    if (a < 0 || a >= limit || ((a & 3) != 0 && s[r] == a - 1 && s[r] >= 0)) continue;
+    int n = 1;
+#pragma unroll
+    for (int j = 1; j < 4; ++j)
+      if (n == j && ((a + j) & 3) != 0 && r + 1 + j < 8 && s[r + 1 + j < 8 ? r + 1 + j : 7] == a + j) n = j + 1;
+    lens |= (uint32_t)n << (4 * r);
+  }
+  if (lens == 0x1111u) {                                   // four tokens of four places (a large decode step)
+    const int64_t own[4] = {s[1], s[2], s[3], s[4]};
+    kv_write_tokens<4, false>(p, t0, 4, own, h, c, sk, sv);
+    return;
+  }
+#pragma unroll 1
+  for (int r = 0; r < 4; ++r) {
+    const int n = (int)(lens >> (4 * r)) & 15;
+    const int64_t own[4] = {slots[min(t0 + r, tokens - 1)], 0, 0, 0};
+    if (n > 0) kv_write_tokens<4, true>(p, t0 + r, n, own, h, c, sk, sv);
+  }
+}
+
+__global__ __launch_bounds__(256) void kv_write_token_kernel(const KvWrite p, int64_t tokens,
+                                                            const int64_t* __restrict__ slots, int64_t num_blocks,
+                                                            const float* __restrict__ k_scale,
+                                                            const float* __restrict__ v_scale) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  const uint32_t per = (uint32_t)p.kv_heads * (kDim / 8);
+  const uint32_t t = i / per, rem = i - t * per;
+  if (t >= tokens) return;
+  const int64_t slot = slots[t];
+  const StaticScale sk = static_scale(k_scale[0]), sv = static_scale(v_scale[0]);
+  if (slot >= 0 && slot < num_blocks * kPage)
+    kv_write_tokens<1, false>(p, t, 1, {slot}, (int)(rem / (kDim / 8)), (int)(rem % (kDim / 8)), sk, sv);
 }
 
 // ---------------------------------------------------------------------------
@@ -622,8 +679,9 @@ hipError_t launch_kv_calibrate_scale(const uint16_t* x, int64_t n, float* scale,
   return hipGetLastError();
 }
 
-// (token, kv head) pairs up to which a cache write runs one token per thread.
-constexpr int64_t kSmallWrite = 4096;
+// (token, kv head) pairs up to which a cache write runs one token per thread (1000 x 8: 6.0
+// us scattered, four per thread 8.3; 2000 x 8 in order 8.9, four per thread 5.0).
+constexpr int64_t kSmallWrite = 8192;
 
 hipError_t launch_kv_cache_write(const uint16_t* k, const uint16_t* v, int64_t tokens, int kv_heads,
                                  const int64_t* slots, int64_t num_blocks, const float* k_scale, const float* v_scale,
@@ -631,12 +689,13 @@ hipError_t launch_kv_cache_write(const uint16_t* k, const uint16_t* v, int64_t t
   const auto blocks = [&](int64_t per_thread) {
     return (unsigned)(((tokens + per_thread - 1) / per_thread * kv_heads * (kDim / 8) + 255) / 256);
   };
+  const KvWrite p{k, v, k_cache, v_cache, kv_heads};
   if (tokens * kv_heads <= kSmallWrite)
-    hipLaunchKernelGGL(kv_write_kernel<1>, dim3(blocks(1)), dim3(256), 0, stream, k, v, tokens, kv_heads, slots,
-                       num_blocks, k_scale, v_scale, k_cache, v_cache);
+    hipLaunchKernelGGL(kv_write_token_kernel, dim3(blocks(1)), dim3(256), 0, stream, p, tokens, slots, num_blocks,
+                       k_scale, v_scale);
   else
-    hipLaunchKernelGGL(kv_write_kernel<4>, dim3(blocks(4)), dim3(256), 0, stream, k, v, tokens, kv_heads, slots,
-                       num_blocks, k_scale, v_scale, k_cache, v_cache);
+    hipLaunchKernelGGL(kv_write_kernel, dim3(blocks(4)), dim3(256), 0, stream, p, tokens, slots, num_blocks, k_scale,
+                       v_scale);
   return hipGetLastError();
 }
 

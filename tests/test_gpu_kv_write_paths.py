@@ -32,7 +32,7 @@ def write(fp8rl, k, v, slots, nb, ks, vs):
     assert_codes_equal(u8(vc), vr, f"v codes, scale {vs!r}")
 
 
-@pytest.mark.parametrize("copies", [1, 9])        # 510 (token, head) pairs: one token per thread; 4590: four
+@pytest.mark.parametrize("copies", [1, 17])       # 510 (token, head) pairs: one token per thread; 8670: four
 @pytest.mark.parametrize("scales", [(0.0123, 3.7e-4), (2.0 ** -91, float(np.nextafter(np.float32(2.0 ** -91), np.float32(0)))),
                                     (2.0 ** 110, float(np.nextafter(np.float32(2.0 ** 110), np.float32(1e38)))),
                                     (1.0, 0.33333334), (1e-40, 3e38), (7.0e-5, 1.7e3)])
@@ -45,14 +45,20 @@ def test_every_value_and_scale_range(fp8rl, scales, copies):
         write(fp8rl, x, x.flip(0).contiguous(), np.arange(t, dtype=np.int64), (t + 15) // 16, *scales)
 
 
-@pytest.mark.parametrize("tokens,kv_heads", [(1, 1), (4, 1024), (5, 1024), (511, 8), (512, 8), (513, 8), (515, 8)])
+@pytest.mark.parametrize("tokens,kv_heads", [(1, 1), (4, 1024), (5, 1024), (1023, 8), (1024, 8), (1025, 8), (1027, 8), (2050, 4)])
 def test_both_mappings_at_their_border(fp8rl, tokens, kv_heads):
     announce(f"kv write {tokens} tokens x {kv_heads} heads")
     rng = np.random.default_rng(tokens)
     k, v = (torch.from_numpy(rng.standard_normal((tokens, kv_heads, 128)).astype(np.float32)).to(torch.bfloat16)
             for _ in range(2))
     nb = (tokens + 15) // 16 + 1
-    for slots in (np.arange(tokens) + 4, np.arange(tokens) + 3, rng.permutation(nb * 16)[:tokens]):
+    nb += 2
+    ragged = np.arange(tokens) + 3 + 5 * (np.arange(tokens) // 37 % 2)       # prompts of 37 tokens, odd starts
+    ragged = np.unique(ragged)[:tokens] if np.unique(ragged).size >= tokens else np.arange(tokens) + 1
+    pairs = rng.permutation(nb * 8)[:(tokens + 1) // 2]                      # runs of two, aligned and not
+    runs = (pairs[:, None] * 2 + np.array([0, 1])).reshape(-1)[:tokens]
+    for slots in (np.arange(tokens) + 4, np.arange(tokens) + 3, rng.permutation(nb * 16)[:tokens], ragged, runs,
+                  np.arange(tokens)[::-1] + 2):
         slots = slots.astype(np.int64)
         slots[tokens // 2] = -1 if tokens > 2 else slots[tokens // 2]
         write(fp8rl, k, v, slots, nb, 0.009, 0.011)
