@@ -40,9 +40,10 @@ using Cfg128x64 = GemmCfg<128, 64, 2, 2, 3>;   // two groups: 512 threads, wave 
 using Cfg128x128 = GemmCfg<128, 128, 2, 4, 4>; // 512 threads, wave tile 64 x 32, 130 KiB LDS
 using Cfg128x256 = GemmCfg<128, 256, 2, 4, 3>; // 512 threads, wave tile 64 x 64, 147 KiB LDS
 using Cfg256x128 = GemmCfg<256, 128, 4, 2, 3>; // 512 threads, wave tile 64 x 64, 146 KiB LDS
-// Split-K ranges: one tile per workgroup, 2 K steps in flight (2 / 3 / 4 slots: decode
-// linears 129 / 123 / 125 us per layer).
-using CfgSplitK = GemmCfg<128, 128, 2, 2, 3>;
+// Split-K ranges: one 128x128 tile per workgroup with eight waves (gemm_pipe; down, K =
+// 12288, with its reduction: M = 256 29.9 us on four waves and a 3-slot ring of
+// gemm_tiles, 29.0 now; M = 300 44.4, 36.5 now).
+using CfgSplitK = Cfg128x128;
 // The grouped GEMM: 128x128, two persistent workgroups per CU (gate_up of the expert
 // block, 4096 tokens: 177 us; 256n x 128m 197, 128n x 64m 216, gemm_pipe with one
 // workgroup per CU walking 256n x 128m / 128x128 tiles 196 / 212; down, K = 768: 108
@@ -130,8 +131,7 @@ __global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_kernel(
     uint16_t* __restrict__ y, int64_t ldy, int64_t M, int64_t N, int KB, int tiles_m, int tiles_n) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[C::kLdsBytes];
   DenseJobs<C> jobs{(int)blockIdx.x, (int)gridDim.x, tiles_m, tiles_n, (int)M};
-  gemm_tiles<C, false, kCrossTiles<C>, DenseJobs<C>, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, KB, y, ldy, nullptr,
-                                                          (int)N, KB, jobs, lds);
+  gemm_tiles<C, kCrossTiles<C>, DenseJobs<C>, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, KB, y, ldy, (int)N, KB, jobs, lds);
 }
 
 // One tile per workgroup of C::kThreads * WK threads (gemm_pipe.hpp).
@@ -142,7 +142,8 @@ __global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_pipe_kernel(
     uint16_t* __restrict__ y, int64_t ldy, int64_t M, int64_t N, int KB, int tiles_m, int tiles_n) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[kPipeLds<C, WK>];
   DenseJobs<C> jobs{(int)blockIdx.x, (int)gridDim.x, tiles_m, tiles_n, (int)M};
-  gemm_pipe<C, WK, DenseJobs<C>, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, KB, y, ldy, (int)N, KB, jobs, lds);
+  gemm_pipe<C, WK, false, DenseJobs<C>, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, KB, y, ldy, nullptr, (int)N, KB, jobs,
+                                            lds);
 }
 
 // Split-K dense GEMM, for shapes whose tiles alone cannot fill the GPU (decode:
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_splitk_kernel(
   jobs.job.n0 = (tile / tiles_m) * C::BN;
   jobs.job.qw_off = (int64_t)kb0 * 128;
   jobs.job.sw_off = kb0;
-  gemm_tiles<C, true, false>(qa + (int64_t)kb0 * 128, lda, sa + (int64_t)kb0 * ld_sa, ld_sa, qw, ldw, sw, KB, nullptr, 0,
-                      part + (int64_t)split * M * N, (int)N, kb1 - kb0, jobs, lds);
+  gemm_pipe<C, 1, true, OneJob, false>(qa + (int64_t)kb0 * 128, lda, sa + (int64_t)kb0 * ld_sa, ld_sa, qw, ldw, sw, KB,
+                                       nullptr, 0, part + (int64_t)split * M * N, (int)N, kb1 - kb0, jobs, lds);
 }
 
 // y[m][n] = bf16_rne(part[0][m][n] + part[1][m][n] + ... ), eight n per thread.
@@ -284,9 +285,8 @@ __global__ __launch_bounds__(kMfmaBounds) void grouped_gemm_w8a8_block_kernel(
   GroupedJobs<C> jobs{(int)blockIdx.x, (int)gridDim.x, __builtin_amdgcn_readfirstlane(tstart[G]), tiles_n, G,
                       tstart, rstart, N, K};
   const int KB = (int)(K / 128);
-  gemm_tiles<C, false, kCrossTiles<C>, GroupedJobs<C>, kMx, kGather>(qa, kGather ? lda : K, sa, ld_sa, qw, K, sw, KB,
-                                                                     y, N, nullptr, (int)N, KB, jobs, lds, gidx,
-                                                                     src_rows);
+  gemm_tiles<C, kCrossTiles<C>, GroupedJobs<C>, kMx, kGather>(qa, kGather ? lda : K, sa, ld_sa, qw, K, sw, KB, y, N,
+                                                              (int)N, KB, jobs, lds, gidx, src_rows);
 }
 
 // Workgroups that stay resident on one CU for a configuration (LDS-limited).

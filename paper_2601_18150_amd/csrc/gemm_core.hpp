@@ -197,8 +197,7 @@ struct TileJob {
 // must not touch LDS or synchronise).  Rows >= M of a tile are clamped on load
 // and masked on store, weight rows >= N likewise.  Each tile sums KB K blocks
 // starting where qa, sa, qw + qw_off and sw + sw_off point; sw rows (one per
-// 128 weight rows) are sw_ld floats apart.  kPartial: write the fp32 sums to part (rows of
-// N floats) instead of bf16 to y (one K range of a split-K product).
+// 128 weight rows) are sw_ld floats apart.
 //
 // Pipeline (S-slot LDS ring, S = C::STAGES, one barrier per K step):
 //   prologue: the DMA of steps 0 .. S-2 into slots 0 .. S-2.
@@ -226,17 +225,17 @@ struct TileJob {
 // The row indices of the next tile are loaded when that tile is picked, one
 // tile ahead, and turned into DMA offsets at the current tile's last step,
 // after the per-step vmcnt(0) waits have retired them (2-slot ring only).
-template <class C, bool kPartial, bool kCross, class Jobs, bool kMx = false, bool kGather = false>
+template <class C, bool kCross, class Jobs, bool kMx = false, bool kGather = false>
 __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64_t lda,
                                            const float* __restrict__ sa, int64_t ld_sa,
                                            const uint8_t* __restrict__ qw, int64_t ldw,
                                            const float* __restrict__ sw, int sw_ld,
-                                           uint16_t* __restrict__ y, int64_t ldy, float* __restrict__ part,
-                                           int N, int KB, Jobs& jobs, uint8_t* lds,
+                                           uint16_t* __restrict__ y, int64_t ldy, int N,
+                                           int KB, Jobs& jobs, uint8_t* lds,
                                            const int32_t* __restrict__ gidx = nullptr, int src_rows = 0) {
   constexpr int S = C::STAGES;
   static_assert(S == 2 || !kCross, "the cross-tile pipeline is written for a 2-slot ring");
-  static_assert(!kGather || (S == 2 && kCross && !kPartial), "row gather: 2-slot cross-tile pipeline only");
+  static_assert(!kGather || (S == 2 && kCross), "row gather: 2-slot cross-tile pipeline only");
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -473,62 +472,48 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
     //      S = 2) is free once every wave is past the barrier below; with kCross
     //      the other holds the next tile's first K block (in flight).  Without
     //      kCross no DMA is in flight and the whole ring is free.
-    if constexpr (kPartial) {
-      // split-K partial: the fp32 sums, four consecutive n per lane (16 bytes)
+    // fp32 -> bf16 (RNE), staged in LDS, then full 16-byte chunks of whole
+    // output rows with streaming stores.  Direct 8-byte stores from the MFMA
+    // layout wrote partial cache lines (1.6x the output bytes reached HBM)
+    // and let the output displace the operands in the memory-side cache.
+    // Staging layout: rows of BN bf16; 16-byte chunk c of row r (counted
+    // within the row group) sits at c ^ (r & 15) (r & 7 for 64-wide tiles), so the 16 rows of one
+    // fragment store, and the rows of one read-back wave instruction, spread
+    // evenly over the 64 banks.  Row groups of kRows rows fit one slot (or,
+    // without kCross, the whole ring).
+    constexpr int kRowBytes = C::BN * 2;
+    constexpr int kChunks = kRowBytes / 16;
+    constexpr int kSpace = kCross ? C::kStageBytes : C::kLdsBytes;
+    constexpr int kRowsFit = kSpace / kRowBytes;
+    constexpr int kRows = kRowsFit >= C::BM ? C::BM : (kRowsFit / C::WTM) * C::WTM;
+    static_assert(kChunks % 8 == 0 && kRows >= C::WTM && C::BM % kRows == 0, "bf16 staging must fit");
+    // (64-wide tiles: 8 chunks per row, key r & 7, which keeps the XOR inside the row)
+    constexpr int kSwz = kChunks % 16 == 0 ? 15 : 7;
+    uint8_t* stage = kCross ? lds + (slot ^ 1) * C::kStageBytes : lds;
 #pragma unroll
-      for (int tn = 0; tn < C::TN; ++tn) {
-        const int nl = wn * C::WTN + tn * 16 + 4 * fg;
+    for (int g0 = 0; g0 < C::BM; g0 += kRows) {
+      lds_barrier();                       // the staging space is free (last K step / previous group)
+      if (wm * C::WTM >= g0 && wm * C::WTM < g0 + kRows) {
 #pragma unroll
-        for (int tm = 0; tm < C::TM; ++tm) {
-          const int ml = wm * C::WTM + tm * 16 + frow;
-          if (ml < cur.m_valid && nl < n_valid)
-            *reinterpret_cast<v4f32*>(part + (int64_t)(cur.row_lo + ml) * N + cur.n0 + nl) = acc[tn][tm];
+        for (int tn = 0; tn < C::TN; ++tn) {
+          const int nl = wn * C::WTN + tn * 16 + 4 * fg;
+#pragma unroll
+          for (int tm = 0; tm < C::TM; ++tm) {
+            const int ml = wm * C::WTM + tm * 16 + frow - g0;
+            uint2 o;
+            o.x = f32_to_bf16_rne(acc[tn][tm][0]) | (f32_to_bf16_rne(acc[tn][tm][1]) << 16);
+            o.y = f32_to_bf16_rne(acc[tn][tm][2]) | (f32_to_bf16_rne(acc[tn][tm][3]) << 16);
+            *reinterpret_cast<uint2*>(stage + ml * kRowBytes + (((nl >> 3) ^ (ml & kSwz)) << 4) + ((nl >> 2) & 1) * 8) = o;
+          }
         }
       }
-    } else {
-      // fp32 -> bf16 (RNE), staged in LDS, then full 16-byte chunks of whole
-      // output rows with streaming stores.  Direct 8-byte stores from the MFMA
-      // layout wrote partial cache lines (1.6x the output bytes reached HBM)
-      // and let the output displace the operands in the memory-side cache.
-      // Staging layout: rows of BN bf16; 16-byte chunk c of row r (counted
-      // within the row group) sits at c ^ (r & 15) (r & 7 for 64-wide tiles), so the 16 rows of one
-      // fragment store, and the rows of one read-back wave instruction, spread
-      // evenly over the 64 banks.  Row groups of kRows rows fit one slot (or,
-      // without kCross, the whole ring).
-      constexpr int kRowBytes = C::BN * 2;
-      constexpr int kChunks = kRowBytes / 16;
-      constexpr int kSpace = kCross ? C::kStageBytes : C::kLdsBytes;
-      constexpr int kRowsFit = kSpace / kRowBytes;
-      constexpr int kRows = kRowsFit >= C::BM ? C::BM : (kRowsFit / C::WTM) * C::WTM;
-      static_assert(kChunks % 8 == 0 && kRows >= C::WTM && C::BM % kRows == 0, "bf16 staging must fit");
-      // (64-wide tiles: 8 chunks per row, key r & 7, which keeps the XOR inside the row)
-      constexpr int kSwz = kChunks % 16 == 0 ? 15 : 7;
-      uint8_t* stage = kCross ? lds + (slot ^ 1) * C::kStageBytes : lds;
-#pragma unroll
-      for (int g0 = 0; g0 < C::BM; g0 += kRows) {
-        lds_barrier();                       // the staging space is free (last K step / previous group)
-        if (wm * C::WTM >= g0 && wm * C::WTM < g0 + kRows) {
-#pragma unroll
-          for (int tn = 0; tn < C::TN; ++tn) {
-            const int nl = wn * C::WTN + tn * 16 + 4 * fg;
-#pragma unroll
-            for (int tm = 0; tm < C::TM; ++tm) {
-              const int ml = wm * C::WTM + tm * 16 + frow - g0;
-              uint2 o;
-              o.x = f32_to_bf16_rne(acc[tn][tm][0]) | (f32_to_bf16_rne(acc[tn][tm][1]) << 16);
-              o.y = f32_to_bf16_rne(acc[tn][tm][2]) | (f32_to_bf16_rne(acc[tn][tm][3]) << 16);
-              *reinterpret_cast<uint2*>(stage + ml * kRowBytes + (((nl >> 3) ^ (ml & kSwz)) << 4) + ((nl >> 2) & 1) * 8) = o;
-            }
-          }
-        }
-        lds_barrier();
-        const int c = t % kChunks;             // this thread's chunk of every row it writes
+      lds_barrier();
+      const int c = t % kChunks;             // this thread's chunk of every row it writes
 #pragma unroll 4
-        for (int r = t / kChunks; r < kRows; r += C::kThreads / kChunks) {
-          if (g0 + r < cur.m_valid && c * 8 < n_valid) {
-            const uint4 v = *reinterpret_cast<const uint4*>(stage + r * kRowBytes + ((c ^ (r & kSwz)) << 4));
-            store_stream16(y + (int64_t)(cur.row_lo + g0 + r) * ldy + cur.n0 + c * 8, v);
-          }
+      for (int r = t / kChunks; r < kRows; r += C::kThreads / kChunks) {
+        if (g0 + r < cur.m_valid && c * 8 < n_valid) {
+          const uint4 v = *reinterpret_cast<const uint4*>(stage + r * kRowBytes + ((c ^ (r & kSwz)) << 4));
+          store_stream16(y + (int64_t)(cur.row_lo + g0 + r) * ldy + cur.n0 + c * 8, v);
         }
       }
     }

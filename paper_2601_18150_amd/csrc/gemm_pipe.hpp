@@ -28,11 +28,13 @@ namespace fp8rl {
 template <class C, int WK>
 constexpr int kPipeLds = WK * C::kLdsBytes;
 
-template <class C, int WK, class Jobs, bool kMx>
+// kPartial: the fp32 sums of a K range to part (rows of N floats) instead of bf16 to y.
+template <class C, int WK, bool kPartial, class Jobs, bool kMx>
 __device__ __forceinline__ void gemm_pipe(const uint8_t* __restrict__ qa, int64_t lda, const float* __restrict__ sa,
                                           int64_t ld_sa, const uint8_t* __restrict__ qw, int64_t ldw,
                                           const float* __restrict__ sw, int sw_ld, uint16_t* __restrict__ y,
-                                          int64_t ldy, int N, int KB, Jobs& jobs, uint8_t* lds) {
+                                          int64_t ldy, float* __restrict__ part, int N, int KB, Jobs& jobs,
+                                          uint8_t* lds) {
   constexpr int S = C::STAGES;
   static_assert(C::WTN <= 64 && C::WTM <= 64, "two fragment sets fit the registers");
   constexpr int kPer = C::kLoadsPerWave;
@@ -182,6 +184,20 @@ __device__ __forceinline__ void gemm_pipe(const uint8_t* __restrict__ qa, int64_
         for (int i = 0; i < kSub; ++i) acc[i / C::TM][i % C::TM] += red[(i * C::kWaves + wave) * 64 + lane];
       }
     }
+  }
+  if constexpr (kPartial) {
+    static_assert(WK == 1, "the groups' sums are not split further");
+#pragma unroll
+    for (int tn = 0; tn < C::TN; ++tn) {
+      const int nl = wn * C::WTN + tn * 16 + 4 * fg;
+#pragma unroll
+      for (int tm = 0; tm < C::TM; ++tm) {
+        const int ml = wm * C::WTM + tm * 16 + frow;
+        if (ml < job.m_valid && nl < n_valid)
+          *reinterpret_cast<v4f32*>(part + (int64_t)(job.row_lo + ml) * N + job.n0 + nl) = acc[tn][tm];
+      }
+    }
+    return;
   }
   // bf16 through LDS, whole 16-byte chunks of output rows with streaming stores
   // (layout as in gemm_tiles)
