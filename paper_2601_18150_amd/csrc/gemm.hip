@@ -339,29 +339,61 @@ struct TileChoice {
   double step;      // rounds x step time, us per K block
 };
 
+struct TileCost {
+  Tile tile;
+  int bn, bm;
+  double one, more;      // us per K block: a single round, each of several
+};
+constexpr TileCost kTileCosts[] = {
+    {Tile::k64x64, 64, 64, 0.32, 0.32},     {Tile::k64x128, 64, 128, 0.49, 0.49},
+    {Tile::k128x64, 128, 64, 0.49, 0.49},   {Tile::k128x128, 128, 128, 0.66, 0.66},
+    {Tile::k128x256, 128, 256, 1.2, 1.2},   {Tile::k256x128, 256, 128, 1.2, 1.2},
+    {Tile::k256x256, 256, 256, 1.5, 1.75},
+};
+
 // The smallest rounds x step time (figures at the configurations above).
 TileChoice tile_for(int64_t m, int64_t n) {
-  struct Cost {
-    Tile tile;
-    int bn, bm;
-    double one, more;      // us per K block: a single round, each of several
-  };
-  static constexpr Cost kCosts[] = {
-      {Tile::k64x64, 64, 64, 0.32, 0.32},     {Tile::k64x128, 64, 128, 0.49, 0.49},
-      {Tile::k128x64, 128, 64, 0.49, 0.49},   {Tile::k128x128, 128, 128, 0.66, 0.66},
-      {Tile::k128x256, 128, 256, 1.2, 1.2},   {Tile::k256x128, 256, 128, 1.2, 1.2},
-      {Tile::k256x256, 256, 256, 1.5, 1.75},
-  };
   const int64_t pairs = ((m + 127) / 128) * (n / 128) / 512, rest = ((m + 127) / 128) * (n / 128) % 512;
   TileChoice best{Tile::kPersistent, 1.25 * (double)pairs + (rest == 0 ? 0.0 : rest <= 256 ? 0.9 : 1.25)};
   if (pairs > 0 && rest > 0 && rest <= 256) best.step -= 0.15;
-  for (const Cost& c : kCosts) {
+  for (const TileCost& c : kTileCosts) {
     const int64_t tiles = ((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
     const int64_t rounds = (tiles + kCus - 1) / kCus;
     const double step = rounds == 1 ? c.one : c.more * (double)rounds;
     if (step < best.step) best = {c.tile, step};
   }
   return best;
+}
+
+// A nearly empty last round costs almost as much as a full one.  Where that is dear,
+// the first n1 output columns run as whole rounds of 256x256 tiles and the others as a
+// product of their own with the tile that suits them (n1 = 0: one launch for all), if
+// the table promises a tenth with the second launch's 3 us counted.  Qwen3-8B, one
+// launch / two, us: gate_up M = 777 106.7 / 96.5, M = 1000 110.9 / 103.1, M = 1300 160.3 /
+// 149.6; M = 3001 qkv 92.4 / 80.6; M = 5000 down 267 / 246.  Smaller promises are within
+// the table's error (gate_up M = 1600, 5%: 169 / 170; M = 3001, 3%: 283 / 293), and so were
+// those of the smaller tiles (M = 1300 down, 4%: 89.8 / 98.5).
+struct ColumnSplit {
+  int64_t n1;
+  Tile first;
+  Tile rest;             // (n1 = 0: the tile of the whole product)
+};
+
+ColumnSplit column_split(int64_t m, int64_t n, int64_t k) {
+  const double kb = (double)(k / 128);
+  const TileChoice whole = tile_for(m, n);
+  const TileCost& c = kTileCosts[sizeof(kTileCosts) / sizeof(kTileCosts[0]) - 1];
+  static_assert(kTileCosts[sizeof(kTileCosts) / sizeof(kTileCosts[0]) - 1].tile == Tile::k256x256, "the last entry");
+  const int64_t tiles_m = (m + c.bm - 1) / c.bm;
+  if (tiles_m <= kCus) {
+    const int64_t per_round = kCus / tiles_m, rounds = n / c.bn / per_round, n1 = rounds * per_round * c.bn;
+    if (rounds >= 1 && n1 < n) {
+      const TileChoice rest = tile_for(m, n - n1);
+      const double both = ((rounds == 1 ? c.one : c.more * (double)rounds) + rest.step) * kb + 3.0;
+      if (both < 0.9 * whole.step * kb) return {n1, c.tile, rest.tile};
+    }
+  }
+  return {0, c.tile, whole.tile};
 }
 
 template <class C, int WK, bool kMx>
@@ -402,9 +434,18 @@ hipError_t launch_gemm_w8a8_block(const uint8_t* qa, int64_t lda, const float* s
                                   int64_t m, int64_t n, int64_t k, hipStream_t stream, bool pow2_scales) {
   if (m <= kSmallTokens && n < kSmallMaxN)
     return launch_gemm_small(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream, pow2_scales);
-  const Tile tile = tile_for(m, n).tile;
-  return pow2_scales ? launch_tile<true>(tile, qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
-                     : launch_tile<false>(tile, qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream);
+  const auto columns = [&](Tile tile, int64_t n0, int64_t cols) {
+    const uint8_t* w = qw + n0 * ldw;
+    const float* s = sw + n0 / 128 * (k / 128);
+    return pow2_scales ? launch_tile<true>(tile, qa, lda, sa, ld_sa, w, ldw, s, y + n0, ldy, m, cols, k, stream)
+                       : launch_tile<false>(tile, qa, lda, sa, ld_sa, w, ldw, s, y + n0, ldy, m, cols, k, stream);
+  };
+  const ColumnSplit c = column_split(m, n, k);
+  if (c.n1 > 0) {
+    const hipError_t e = columns(c.first, 0, c.n1);
+    if (e != hipSuccess) return e;
+  }
+  return columns(c.rest, c.n1, n - c.n1);
 }
 
 // Decode batches (128 < M <= 256) whose 64x64 tiles number at most 512 (two per CU).

@@ -29,6 +29,7 @@ def fp8rl():
     (640, 24704, 128), (600, 24576, 5 * 128),                                           # 256x128, last tile of 128
     (1300, 6272, 128), (300, 24704, 384),                                               # 256x256, last tile of 128
     (1400, 12800, 256),                                                                 # persistent 128x128
+    (777, 24576, 9 * 128), (3001, 6272, 7 * 128), (2100, 6144, 1024),                   # columns in two launches
 ])
 def test_dense_tile_choices(fp8rl, m, n, k):
     announce(f"gemm tiles m={m} n={n} k={k}")
