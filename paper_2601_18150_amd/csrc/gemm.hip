@@ -82,11 +82,10 @@ __device__ __forceinline__ int xcd_grouped_tile(int id, int tiles_m, int tiles_n
 }
 
 // The cross-tile pipeline (next tile's first load during this tile's last
-// step) for the 128x128 and 256x128 tiles with a 2-slot ring; the 256x256 tile
-// has no registers to spare for the next tile's load plan and runs one tile per
-// workgroup.
+// step) for the 128x128 tiles; the 256x256 tile has no registers to spare for
+// the next tile's load plan and runs one tile per workgroup.
 template <class C>
-constexpr bool kCrossTiles = C::BN * C::BM <= 256 * 128 && C::STAGES == 2;
+constexpr bool kCrossTiles = C::BN * C::BM <= 128 * 128;
 
 // Job providers for gemm_tiles (see gemm_core.hpp): wave-uniform, no LDS
 // writes, no synchronisation.
@@ -319,8 +318,8 @@ hipError_t launch_grouped(const uint8_t* qa, const float* sa, int64_t ld_sa, con
   const int64_t max_tiles_m = rows / C::BM + g;        // upper bound on the real m tiles
   const int64_t tiles_n = (n + C::BN - 1) / C::BN;
   const int64_t total = max_tiles_m * tiles_n;
-  // persistent grid with the cross-tile pipeline, else one workgroup per tile
-  const int64_t slots = kCrossTiles<C> ? (int64_t)kCus * per_cu<C, 2 * 4 * (kMaxExperts + 1)>() : total;
+  static_assert(kCrossTiles<C>, "the grouped grid is persistent");
+  const int64_t slots = (int64_t)kCus * per_cu<C, 2 * 4 * (kMaxExperts + 1)>();
   hipLaunchKernelGGL((grouped_gemm_w8a8_block_kernel<C, kMx, kGather>),
                      dim3((unsigned)(total < slots ? total : slots)), dim3(C::kThreads), 0, stream, qa, sa, ld_sa, qw,
                      sw, offsets, (int)g, y, n, k, (int)tiles_n, gidx, (int)src_rows, lda);

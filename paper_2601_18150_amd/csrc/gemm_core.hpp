@@ -151,23 +151,10 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
-// At the top of a K step with `later` further steps' DMA already issued behind
-// it (kPer wave instructions each), wait until this step's DMA has landed.
-// Loads complete in issue order, so vmcnt(later * kPer) suffices; the count
-// must be an immediate, hence the branches (later <= S - 2).
-template <int S, int kPer>
-__device__ __forceinline__ void wait_dma_step(int later) {
-  static_assert(S >= 2 && (S - 2) * kPer < 64, "vmcnt is 6 bits");
-  if constexpr (S > 2) {
-    if (later >= S - 2) { wait_vmcnt<(S - 2) * kPer>(); return; }
-    wait_dma_step<S - 1, kPer>(later);
-  } else {
-    wait_vmcnt<0>();
-  }
-}
-
-// The same for a ring of D slots that one wave refills itself, `later` further
-// fetches of kPer instructions each issued behind the one waited for.
+// For a ring of D slots that one wave refills itself, with `later` further
+// fetches of kPer instructions each issued behind the one it needs: wait until
+// that one has landed.  Loads complete in issue order, so vmcnt(later * kPer)
+// suffices; the count must be an immediate, hence the branches (later <= D - 1).
 template <int kPer, int D>
 __device__ __forceinline__ void wait_own_ring(int later) {
   static_assert((D - 1) * kPer < 64, "vmcnt is 6 bits");
@@ -199,13 +186,12 @@ struct TileJob {
 // starting where qa, sa, qw + qw_off and sw + sw_off point; sw rows (one per
 // 128 weight rows) are sw_ld floats apart.
 //
-// Pipeline (S-slot LDS ring, S = C::STAGES, one barrier per K step):
-//   prologue: the DMA of steps 0 .. S-2 into slots 0 .. S-2.
+// Pipeline (two LDS slots, one barrier per K step):
+//   prologue: the DMA of step 0 into slot 0.
 //   step s:  wait for this wave's DMA of step s; barrier (all waves' DMA of step
 //            s landed, all waves done reading step s-1's slot); MFMA + scale-FMA
-//            on slot s % S, with the DMA of step s+S-1 into the slot of step s-1
-//            interleaved.  S - 1 K steps are in flight while one is computed.
-//   kCross (2-slot ring only): after a tile's last K block, step s+1 is the
+//            on slot s % 2, with the DMA of step s+1 into the other interleaved.
+//   kCross:  after a tile's last K block, step s+1 is the
 //            first K block of the workgroup's next tile, so consecutive tiles
 //            form one pipeline and the next tile's first load overlaps this
 //            tile's last step and output.  Without it the workgroup computes its
@@ -224,7 +210,7 @@ struct TileJob {
 // [0, src_rows)), so a gather of quantised rows (MoE dispatch) needs no copy.
 // The row indices of the next tile are loaded when that tile is picked, one
 // tile ahead, and turned into DMA offsets at the current tile's last step,
-// after the per-step vmcnt(0) waits have retired them (2-slot ring only).
+// after the per-step vmcnt(0) waits have retired them (kCross only).
 template <class C, bool kCross, class Jobs, bool kMx = false, bool kGather = false>
 __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64_t lda,
                                            const float* __restrict__ sa, int64_t ld_sa,
@@ -233,9 +219,8 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
                                            uint16_t* __restrict__ y, int64_t ldy, int N,
                                            int KB, Jobs& jobs, uint8_t* lds,
                                            const int32_t* __restrict__ gidx = nullptr, int src_rows = 0) {
-  constexpr int S = C::STAGES;
-  static_assert(S == 2 || !kCross, "the cross-tile pipeline is written for a 2-slot ring");
-  static_assert(!kGather || (S == 2 && kCross), "row gather: 2-slot cross-tile pipeline only");
+  static_assert(C::STAGES == 2, "written for a 2-slot ring");
+  static_assert(!kGather || kCross, "row gather: cross-tile pipeline only");
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -314,19 +299,16 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
   // this lane's activation-scale row of a tile (the scale DMA of waves < kScaleLoads)
   auto sa_lane_cur = [&]() { return kGather ? sa + srow_c : sa_lane_of(cur); };
 
-  // prologue: the first tile's first S-1 K blocks into slots 0 .. S-2
-#pragma unroll
-  for (int p = 0; p < S - 1; ++p) {
-    if (p > 0 && p >= KB) break;
-    const uint8_t* wb = qw + cur.qw_off + (int64_t)cur.n0 * ldw + p * 128;
-    const uint8_t* ab = (kGather ? qa : qa + (int64_t)cur.row_lo * lda) + p * 128;
-    uint8_t* ps = lds + p * C::kStageBytes;
+  // prologue: the first tile's first K block into slot 0
+  {
+    const uint8_t* wb = qw + cur.qw_off + (int64_t)cur.n0 * ldw;
+    const uint8_t* ab = kGather ? qa : qa + (int64_t)cur.row_lo * lda;
 #pragma unroll
     for (int i = 0; i < C::kLoadsPerWave; ++i) {
       const int o = wave + i * C::kWaves;
-      lds_dma16((o < C::BN / 8 ? wb : ab) + goff[i], ps + o * 1024);
+      lds_dma16((o < C::BN / 8 ? wb : ab) + goff[i], lds + o * 1024);
     }
-    if (sdma) lds_dma4(sa_lane_cur() + (int64_t)p * ld_sa, ps + C::kWBytes + C::kABytes + wave * 256);
+    if (sdma) lds_dma4(sa_lane_cur(), lds + C::kWBytes + C::kABytes + wave * 256);
   }
 
   int slot = 0;
@@ -349,13 +331,11 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
       for (int j = 0; j < C::TM; ++j) acc[i][j] = (v4f32){0.f, 0.f, 0.f, 0.f};
 
     for (int kb = 0; kb < KB; ++kb) {
-      // this step's DMA (with S = 2 also a previous tile's output stores)
-      const int later = min(S - 2, KB - 1 - kb);
-      if (sdma) wait_dma_step<S, C::kLoadsPerWave + 1>(later);
-      else wait_dma_step<S, C::kLoadsPerWave>(later);
+      // this step's DMA (and a previous tile's output stores)
+      wait_vmcnt<0>();
       lds_barrier();
 
-      // refill the slot of step s-1 with step s+S-1: a later K block of this
+      // refill the slot of step s-1 with step s+1: the next K block of this
       // tile or, with kCross after its last, the first K block of the next tile
       // (if any).  With 8
       // sub-tile rows per wave the DMA instructions are spread over the first
@@ -364,12 +344,12 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
       // barrier); with fewer, all are issued with the first one (measured
       // fastest for the 128x128 tiles).
       const bool last = kb + 1 == KB;
-      const bool refill = kb + S - 1 < KB || (last && has_nxt);
-      uint8_t* dslot = lds + (slot == 0 ? S - 1 : slot - 1) * C::kStageBytes;
+      const bool refill = !last || has_nxt;
+      uint8_t* dslot = lds + (slot ^ 1) * C::kStageBytes;
       const uint8_t* dwb = wbase;
       const uint8_t* dab = abase;
-      uint32_t dsoff = (kb + S - 1) * 128;
-      const float* dsa = sa_lane + (int64_t)(kb + S - 1) * ld_sa;
+      uint32_t dsoff = (kb + 1) * 128;
+      const float* dsa = sa_lane + (int64_t)(kb + 1) * ld_sa;
       if constexpr (kCross) {
         if (last) {
           dwb = qw + nxt.qw_off + (int64_t)nxt.n0 * ldw;
@@ -402,7 +382,7 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
           }
           if (sdma) lds_dma4(dsa, dslot + C::kWBytes + C::kABytes + wave * 256);
         }
-        slot = slot + 1 == S ? 0 : slot + 1;
+        slot ^= 1;
         continue;
       }
       float sc[C::TM];
@@ -465,11 +445,10 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
         }
         af = af_next;
       }
-      slot = slot + 1 == S ? 0 : slot + 1;
+      slot ^= 1;
     }
 
-    // ---- tile end.  The slot of the last K step (slot ^ 1 now; kCross, so
-    //      S = 2) is free once every wave is past the barrier below; with kCross
+    // ---- tile end.  The slot of the last K step (slot ^ 1 now) is free once every wave is past the barrier below; with kCross
     //      the other holds the next tile's first K block (in flight).  Without
     //      kCross no DMA is in flight and the whole ring is free.
     // fp32 -> bf16 (RNE), staged in LDS, then full 16-byte chunks of whole

@@ -29,13 +29,13 @@ hipError_t launch_small(const SmallArgs& a, hipStream_t stream) {
 
 // The tile: as many activation octets as the tokens need, and 32 instead of 16
 // weight rows per wave (which halves the activation reads per weight byte) where
-// that still leaves 160 workgroups.  Measured on the Qwen3-8B linears, weights
-// from HBM, us per call of a graph replay, 16 / 32 rows (bold layer: the side
-// taken): M = 8 qkv 7.5 / 7.1, o_proj 5.6 / 6.4, gate_up 19.9 / 22.1, down 11.3 /
-// 13.9 (16 rows throughout); M = 16 qkv 8.4 / 7.5, o_proj 6.1 / 6.8, gate_up 22.6 /
-// 22.1, down 12.5 / 15.8; M = 32 qkv 9.9 / 8.6, o_proj 6.7 / 7.9, gate_up 27.4 /
-// 24.1, down 15.2 / 19.0; M = 64 qkv 14.5 / 11.0, o_proj 8.6 / 10.2, gate_up 41.9 /
-// 31.9, down 20.6 / 25.7.
+// that still leaves 160 workgroups; up to 8 tokens always 16.  Measured on the
+// Qwen3-8B linears, weights from HBM, us per call of a graph replay, 16 / 32
+// rows: M = 8 qkv 7.5 / 7.1, o_proj 5.6 / 6.4, gate_up 19.9 / 22.1, down 11.3 /
+// 13.9; M = 16 qkv 8.4 / 7.5, o_proj 6.1 / 6.8, gate_up 22.6 / 22.1, down 12.5 /
+// 15.8; M = 32 qkv 9.9 / 8.6, o_proj 6.7 / 7.9, gate_up 27.4 / 24.1, down 15.2 /
+// 19.0; M = 64 qkv 14.5 / 11.0, o_proj 8.6 / 10.2, gate_up 41.9 / 31.9, down
+// 20.6 / 25.7.
 template <bool kMx>
 hipError_t small_by_shape(const SmallArgs& a, hipStream_t stream) {
   const bool wide = a.n / 32 >= 160;
