@@ -163,9 +163,9 @@ int fp8rl_gemm_w8a8_block(const uint8_t* qa, int64_t lda, const float* sa, int64
  * or a NULL workspace with workspace_bytes > 0, FP8RL_ERR_MISALIGNED for a
  * workspace not 16-byte aligned.  The split result is deterministic and meets
  * the same tolerance; it is not bit-identical to the unsplit path (the K
- * blocks are summed in a different fp32 order).  Calls of at most 64 tokens run
- * the few-token kernel of fp8rl_gemm_w8a8_block whatever the workspace, and
- * leave it untouched.
+ * blocks are summed in a different fp32 order).  Calls of at most 64 tokens, and
+ * those whose unsplit tiles are faster than the ranges and their reduction, run
+ * fp8rl_gemm_w8a8_block's kernel whatever the workspace, and leave it untouched.
  */
 int64_t fp8rl_gemm_w8a8_block_workspace_size(int64_t m, int64_t n, int64_t k);
 
@@ -185,7 +185,7 @@ int fp8rl_gemm_w8a8_block_ws(const uint8_t* qa, int64_t lda, const float* sa, in
  * fp8rl_gemm_w8a8_block_workspace_size(m, n, k) bytes (bit-identical output).
  * FP8RL_ERR_SCRATCH_LIMIT (nothing launched) when that size exceeds the static
  * array; with the current split rule no valid shape needs more than 16 MiB.
- * Calls of at most 64 tokens do not use the array.
+ * Calls that fp8rl_gemm_w8a8_block_ws would run unsplit do not use the array.
  * The array keeps the last call's contents and needs no clearing (every partial
  * sum read is written first by the same call).  Calls that overlap in time on
  * one GPU (concurrent streams or threads) share the array and race: serialise
