@@ -36,6 +36,10 @@ namespace {
 constexpr int kDim = 128;          // head dimension
 constexpr int kPage = 16;          // tokens per cache block
 constexpr float kE4M3Max = 448.0f;
+// A running maximum before its first score: finite, so that scores of -inf (a query-key
+// product past the range of fp32) weigh exp(-inf) = 0 also where they are the first ones
+// seen, instead of exp(-inf + inf) = NaN; below or equal to every finite score.
+constexpr float kNoScore = -3.4028234663852886e38f;
 
 typedef __bf16 v8bf16_t __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf16_t __attribute__((ext_vector_type(2)));
@@ -439,7 +443,7 @@ __device__ __forceinline__ void attn_decode_split_of(
     for (int o = 0; o < kOct; ++o) lds_dma16(rv, lane * 16, o * 1024, dst + kHalf + o * 1024);
   };
 
-  float m = -INFINITY, l = 0.0f;                 // head j: running max; sum over this lane's tokens
+  float m = kNoScore, l = 0.0f;                  // head j: running max; sum over this lane's tokens
   v4f32_t o[8];
 #pragma unroll
   for (int nb = 0; nb < 8; ++nb) o[nb] = (v4f32_t){0.f, 0.f, 0.f, 0.f};
@@ -487,8 +491,8 @@ __device__ __forceinline__ void attn_decode_split_of(
       s[r] = (4 * g + r < valid) ? acc[r] * sscale : -INFINITY;
       mx = fmaxf(mx, s[r]);
     }
-    const float m_new = fmaxf(m, max_over_rows(mx));        // finite: the page has a valid token
-    const float alpha = __expf(m - m_new);                  // 0 on the first page
+    const float m_new = fmaxf(m, max_over_rows(mx));
+    const float alpha = __expf(m - m_new);                  // (first page: whatever it is, o and l are 0)
     l *= alpha;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -538,7 +542,7 @@ __device__ __forceinline__ void attn_decode_split_of(
   l += shfl_xor_f(l, 32);
 
   // ---- combine the four waves: each leaves o[G][128], m[G], l[G] in LDS (a wave
-  //      without pages m = -inf, l = 0, o = 0), then every thread adds its outputs
+  //      without pages m = kNoScore, l = 0, o = 0), then every thread adds its outputs
   float* comb = reinterpret_cast<float*>(lds);
   __syncthreads();                               // the rings are idle (every wave waited for its last DMA)
   {
@@ -560,7 +564,7 @@ __device__ __forceinline__ void attn_decode_split_of(
   float* rec = partial + (((int64_t)b * kv_heads + kvh) * max_splits + split) * partial_floats<kG>();
   for (int e = threadIdx.x; e < kG * kDim / 2; e += 256) {
     const int head = e / (kDim / 2), d = 2 * (e % (kDim / 2));
-    float mm = -INFINITY;
+    float mm = kNoScore;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, comb[w * kComb + kG * kDim + head]);
     float ls = 0.0f, a0 = 0.0f, a1 = 0.0f;
@@ -614,14 +618,14 @@ __global__ __launch_bounds__(32 * kMergeSets) void attn_merge_kernel(
   const int n = min(seq_lens[b], max_seq_len);
   const int ns = min(max_splits, (max(n, 0) + split_pages * kPage - 1) / (split_pages * kPage));
   const float* base = partial + ((int64_t)b * kv_heads + kvh) * max_splits * partial_floats<kG>();
-  float m = -INFINITY, l = 0.0f;
+  float m = kNoScore, l = 0.0f;
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
   for (int s = set; s < ns; s += kMergeSets) {
     const float* r = base + (int64_t)s * partial_floats<kG>();
     const float ms = r[rec_m<kG>() + h], ls = r[rec_l<kG>() + h];
     const float4 o = *reinterpret_cast<const float4*>(r + h * kDim + d);
-    const float mn = fmaxf(m, ms), f = expf(m - mn), w = expf(ms - mn);   // (m = -inf first: f = 0)
+    const float mn = fmaxf(m, ms), f = expf(m - mn), w = expf(ms - mn);
     l = l * f + ls * w;
     a.x = a.x * f + o.x * w;
     a.y = a.y * f + o.y * w;
@@ -637,13 +641,13 @@ __global__ __launch_bounds__(32 * kMergeSets) void attn_merge_kernel(
   }
   __syncthreads();
   if (set != 0) return;
-  float mm = -INFINITY, lsum = 0.0f;
+  float mm = kNoScore, lsum = 0.0f;
 #pragma unroll
   for (int s = 0; s < kMergeSets; ++s) mm = fmaxf(mm, red[s][kDim]);
   a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
   for (int s = 0; s < kMergeSets; ++s) {
-    const float w = ns > 0 ? expf(red[s][kDim] - mm) : 0.0f;              // (a set without splits: 0)
+    const float w = ns > 0 ? expf(red[s][kDim] - mm) : 0.0f;              // (a set without splits adds 0)
     lsum += red[s][kDim + 1] * w;
     a.x += red[s][d] * w;
     a.y += red[s][d + 1] * w;

@@ -37,3 +37,27 @@ def test_attention_split_edges(fp8rl, batch, q_heads, kv_heads, max_len):
     assert ok, f"worst |err|/bound {worst:.3f}"
     assert torch.equal(out.view(torch.int16), again.view(torch.int16)), "not deterministic"
     assert torch.all(out[torch.from_numpy(lens == 0)] == 0)
+
+
+# a split is 16 pages, wave w of it starts at page w: its first page, all first pages, a whole split, all but one token
+@pytest.mark.parametrize("max_len", [256, 1025])
+@pytest.mark.parametrize("pages", [[0], [1], [0, 1, 2, 3], list(range(16)), [5, 6, 15]])
+def test_scores_past_the_range_of_fp32_weigh_nothing(fp8rl, pages, max_len):
+    """Whole pages whose scores overflow to -inf have weight 0 wherever they stand, as one such token among others has
+    (the fp64 oracle's scores do not overflow; their weights underflow to 0)."""
+    announce(f"attention -inf scores in pages {pages}, max_len={max_len}")
+    rng = np.random.default_rng(max_len + len(pages))
+    lens = np.array([max_len, max_len - 5], np.int32)
+    q, kc, vc, table, _ = paged_inputs(rng, lens, 8, 2)
+    q[:, :, 0] = 3.0e38
+    kc[..., 0] = 0                                    # elsewhere: the other 127 dims decide
+    for b in range(len(lens)):
+        for p in pages:
+            kc[table[b, p], :, :, 0] = 0xFE           # -448
+        if max_len == 256 and len(pages) == 16:
+            kc[table[b, 7], :, 3, 0] = 0              # (one token keeps a finite score)
+    ks, vs, sm = np.float32(0.02), np.float32(0.03), float(1 / np.sqrt(128))
+    out = run_fp8(fp8rl, q, kc, vc, table, lens, ks, vs, sm, max_seq_len=max_len)
+    ref = kv.attention_decode(u16(q), kc, vc, ks, vs, table, lens, sm)
+    ok, worst, _ = gemm.tolerance_check(out.float().cpu().numpy().astype(np.float64).reshape(ref.shape), ref)
+    assert ok, f"worst |err|/bound {worst:.3f}"
