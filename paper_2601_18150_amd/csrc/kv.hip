@@ -571,7 +571,7 @@ __device__ __forceinline__ void attn_decode_split_of(
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       const float* c = comb + w * kComb;
-      const float f = __expf(c[kG * kDim + head] - mm);
+      const float f = expf(c[kG * kDim + head] - mm);      // (as in the merge: exact to an ulp far below the maximum too)
       ls += c[kG * kDim + kG + head] * f;
       a0 += c[head * kDim + d] * f;
       a1 += c[head * kDim + d + 1] * f;

@@ -61,3 +61,29 @@ def test_scores_past_the_range_of_fp32_weigh_nothing(fp8rl, pages, max_len):
     ref = kv.attention_decode(u16(q), kc, vc, ks, vs, table, lens, sm)
     ok, worst, _ = gemm.tolerance_check(out.float().cpu().numpy().astype(np.float64).reshape(ref.shape), ref)
     assert ok, f"worst |err|/bound {worst:.3f}"
+
+
+@pytest.mark.parametrize("gap", [-48.0, -60.0, -72.0])
+def test_partial_results_are_combined_in_full_fp32(fp8rl, gap):
+    """One wave of a split scores 0, the other three score `gap` and hold all the value: their 192 tokens' sum in the
+    split's record (fp32, behind the o[128] of the one head: its maximum) is 192 e^gap within 5e-7, two roundings of
+    the weight's ulp and two of the sum; an exponential by a rounded gap * log2(e) is off by 2 to 3e-6 here."""
+    announce(f"attention: combination of the waves, gap {gap}")
+    n = 512                                           # two splits of 16 pages, wave w attends over pages w, w + 4, ...
+    kc, vc = torch.zeros((32, 1, 16, 128)), torch.ones((32, 1, 4, 128, 4))
+    first = torch.arange(32) % 4 == 0
+    kc[~first, :, :, 0] = gap                         # (exact in E4M3)
+    vc[first] = 0
+    kc, vc = (x.to(torch.float8_e4m3fn).view(torch.uint8).cuda() for x in (kc, vc))
+    q = torch.zeros((1, 1, 128), dtype=torch.bfloat16)
+    q[..., 0] = 1.0
+    table = torch.arange(32, dtype=torch.int32).reshape(1, 32)
+    one = torch.ones(1, dtype=torch.float32, device="cuda")
+    need = fp8rl.fp8rl_attention_decode_workspace_size(1, 1, 1, n)
+    ws = torch.full((need // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    fp8rl.fp8rl_attention_decode_fp8kv(q.cuda(), kc, vc, table.cuda(),
+                                       torch.tensor([n], dtype=torch.int32, device="cuda"), n, one, one, 1.0, workspace=ws)
+    torch.cuda.synchronize()
+    rec = ws.cpu().double().reshape(2, -1)[:, :129].numpy()
+    assert np.all(rec[:, 128] == 0.0), "the records' maxima"
+    assert np.all(np.abs(rec[:, :128] / (192 * np.exp(gap)) - 1) < 5e-7), rec[:, 0] / (192 * np.exp(gap)) - 1
