@@ -635,6 +635,5 @@ gather_rows_fp8 = fp8rl_gather_rows_fp8
 def linear_w8a8(x: torch.Tensor, qw: torch.Tensor, sw: torch.Tensor, stream=None) -> torch.Tensor:
     """The W8A8 linear layer's forward: dynamic activation quantisation, then the
     blockwise FP8 GEMM, both on one stream with no host synchronisation."""
-    stream = _stream(stream)
     qa, sa = fp8rl_quant_act_token_group128(x, stream=stream)
     return fp8rl_gemm_w8a8_block(qa, sa, qw, sw, stream=stream)
