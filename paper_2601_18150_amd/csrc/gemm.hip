@@ -110,18 +110,6 @@ struct DenseJobs {
   }
 };
 
-// A single given tile.
-struct OneJob {
-  TileJob job;
-  bool done;
-  __device__ bool next(TileJob& j) {
-    if (done) return false;
-    j = job;
-    done = true;
-    return true;
-  }
-};
-
 // kMx: power-of-two scales through the MX-scaled MFMA (gemm_core.hpp).
 template <class C, bool kMx>
 __global__ __launch_bounds__(kMfmaBounds) void gemm_w8a8_block_kernel(

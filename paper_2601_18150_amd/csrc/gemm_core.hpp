@@ -179,6 +179,18 @@ struct TileJob {
   // the scale reads into vector loads)
 };
 
+// A single given tile.
+struct OneJob {
+  TileJob job;
+  bool done;
+  __device__ bool next(TileJob& j) {
+    if (done) return false;
+    j = job;
+    done = true;
+    return true;
+  }
+};
+
 // Tiles of  Y^T = W . A^T  computed by one workgroup, one after another; the
 // job provider `jobs` hands them out (jobs.next(j) returns false at the end; it
 // must not touch LDS or synchronise).  Rows >= M of a tile are clamped on load

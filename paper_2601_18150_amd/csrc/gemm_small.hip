@@ -54,13 +54,11 @@ template <int WK, bool kMx, bool kGather>
 hipError_t launch_grouped_wk(const uint8_t* qa, int64_t lda, const float* sa, int64_t ld_sa, const uint8_t* qw,
                              const float* sw, const int32_t* offsets, int64_t g, int64_t rows, uint16_t* y, int64_t n,
                              int64_t k, const int32_t* gidx, int64_t src_rows, hipStream_t stream) {
-  // an expert's 32-row chunks go to up to four workgroups, so that a popular
-  // expert's are not one serial chain (96 tokens x 8, gate_up 63.2 -> 61.6 us,
-  // 200 tokens 81.6 -> 77.2; eight instead of four cost the idle ones 2-10 us)
-  const int64_t z = (rows + 31) / 32 < 4 ? (rows + 31) / 32 : 4;
+  // (an expert of r > 0 rows has at most (r - 1) / 32 chunks behind its first)
+  const int64_t extra = rows / kChunkRows;
   hipLaunchKernelGGL((grouped_gemm_small_kernel<WK, kMx, kGather>),
-                     dim3((unsigned)(n / GroupedSmall<WK>::kRows), (unsigned)g, (unsigned)z), dim3(256), 0, stream, qa,
-                     lda, sa, ld_sa, qw, sw, offsets, y, n, k, gidx, (int)src_rows);
+                     dim3((unsigned)(n / GroupedSmall<WK>::kRows), (unsigned)(extra + g)), dim3(256), 0, stream, qa, lda,
+                     sa, ld_sa, qw, sw, offsets, (int)g, (int)extra, y, n, k, gidx, (int)src_rows);
   return hipGetLastError();
 }
 

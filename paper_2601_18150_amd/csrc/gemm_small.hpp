@@ -186,58 +186,144 @@ __global__ __launch_bounds__(kMfmaBounds) void gemm_small_kernel(
                      (uint32_t)min(lane, m - 1), y + n0, ldy, m, KB, lds);
 }
 
-// Grouped, for experts with a few rows each: workgroup (x, e) owns weight rows
-// x * kRows .. of expert e and walks that expert's rows in chunks of 32 (the
-// weight rows come from the L2 after the first), each chunk with the narrowest
-// of three tiles; their rings take about the same LDS.  Experts without rows
-// cost one scalar load.
+// Grouped, for experts with a few rows each on average.  An expert's rows are cut into
+// chunks: of 32 rows, each with the narrowest of three tiles that holds it (their rings
+// take about the same LDS); past kWideFrom rows of 128, on a 64x128 tile of the common K
+// loop in the same LDS, because every chunk streams the expert's weights again.
+// Workgroup (x, `extra` + e) owns weight rows x * kRows .. of expert e's first chunk (an
+// expert without rows costs one scalar load); the further chunks of popular experts are
+// numbered over all experts in order and workgroup (x, c < extra) takes number c, so
+// that they run side by side, first, and are no serial chain however the rows fall.
 template <int WK>
 struct GroupedSmall {
   using R8 = SmallCfg<1, 1, 4, WK, 4>;
   using R16 = SmallCfg<2, 1, 3, WK, 4>;
   using R32 = SmallCfg<4, 1, 2, WK, 4>;
-  static constexpr int kThreads = 256;
+  using Wide = GemmCfg<64, 128, 2, 2, 2>;
   static constexpr int kRows = R8::kRows;
   static constexpr int kMaxOf(int a, int b) { return a > b ? a : b; }
-  static constexpr int kLds = kMaxOf(R8::kLds, kMaxOf(R16::kLds, R32::kLds));
+  static constexpr int kLds = kMaxOf(kMaxOf(R8::kLds, Wide::kLdsBytes), kMaxOf(R16::kLds, R32::kLds));
+  static_assert(R8::kThreads == 256 && Wide::kThreads == 256 && Wide::BN % kRows == 0, "one workgroup for all");
 };
+constexpr int kChunkRows = 32;
+// (one expert of 128 rows, gate_up: four chunks of 32 10.6 us, one wide chunk 12.5; of 256
+// rows: 19.9, wide 18.9)
+constexpr int kWideFrom = 128;
+constexpr int kWideRows = 128;
+
+// The rows of a chunk: r0 .. r1 - 1, of expert e.
+struct RowChunk {
+  int e, r0, r1;
+};
+
+__device__ __forceinline__ int chunk_size(int rows) { return rows > kWideFrom ? kWideRows : kChunkRows; }
+
+// Chunk number c of those behind each expert's first, false past the last (uniform over
+// the workgroup of four waves).  Four experts a lane and one prefix sum for 256 experts:
+// up to that many, every wave looks for itself; more of them (at most 1024) are shared by
+// the four waves.
+constexpr int kFindLds = 8 * 4;
+__device__ __forceinline__ bool find_chunk(const int32_t* __restrict__ offsets, int G, int c, int* lds, RowChunk& out) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool shared = G > 256;
+  const int e = (shared ? 256 * wave : 0) + 4 * lane;
+  int o[5], n[4];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) o[i] = offsets[min(e + i, G)];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) n[i] = max(o[i + 1] - o[i] - 1, 0) / chunk_size(o[i + 1] - o[i]);
+  const int mine = n[0] + n[1] + n[2] + n[3];
+  int upto = wave_inclusive_sum(mine);
+  if (shared) {
+    if (lane == 63) lds[wave] = upto;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < 4; ++w) {
+      const int t = __builtin_amdgcn_readfirstlane(lds[w]);
+      if (w < wave) before += t;
+    }
+    upto += before;
+  }
+  const unsigned long long has = __ballot(upto > c && upto - mine <= c);   // the lane whose four experts hold it
+  if (has) {
+    const int l = __builtin_ctzll(has);
+    int at = c - (upto - mine), i = 0;           // (meaningful in lane l only)
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (i == k && at >= n[k]) {
+        at -= n[k];
+        i = k + 1;
+      }
+    const int lo = i == 0 ? o[0] : i == 1 ? o[1] : i == 2 ? o[2] : o[3];
+    const int hi = i == 0 ? o[1] : i == 1 ? o[2] : i == 2 ? o[3] : o[4];
+    const int size = chunk_size(hi - lo);
+    out.e = __builtin_amdgcn_readlane(e + i, l);
+    out.r0 = __builtin_amdgcn_readlane(lo + (at + 1) * size, l);
+    out.r1 = __builtin_amdgcn_readlane(min(hi, lo + (at + 2) * size), l);
+  }
+  if (!shared) return has != 0;
+  if (has && lane == 0) {
+    lds[4] = out.e;
+    lds[5] = out.r0;
+    lds[6] = out.r1;
+  }
+  const int total = __builtin_amdgcn_readfirstlane(lds[0]) + __builtin_amdgcn_readfirstlane(lds[1]) +
+                    __builtin_amdgcn_readfirstlane(lds[2]) + __builtin_amdgcn_readfirstlane(lds[3]);
+  if (c >= total) return false;
+  __syncthreads();
+  out.e = __builtin_amdgcn_readfirstlane(lds[4]);
+  out.r0 = __builtin_amdgcn_readfirstlane(lds[5]);
+  out.r1 = __builtin_amdgcn_readfirstlane(lds[6]);
+  return true;
+}
 
 template <int WK, bool kMx, bool kGather>
 __global__ __launch_bounds__(kMfmaBounds) void grouped_gemm_small_kernel(
     const uint8_t* __restrict__ qa, int64_t lda, const float* __restrict__ sa, int64_t ld_sa,
-    const uint8_t* __restrict__ qw, const float* __restrict__ sw, const int32_t* __restrict__ offsets,
-    uint16_t* __restrict__ y, int64_t N, int64_t K, const int32_t* __restrict__ gidx, int src_rows) {
-  using G = GroupedSmall<WK>;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[G::kLds];
-  const int e = blockIdx.y;
-  const int r0 = offsets[e], r1 = offsets[e + 1];
-  const int n0 = blockIdx.x * G::kRows;
-  const int lane = threadIdx.x & 63;
+    const uint8_t* __restrict__ qw, const float* __restrict__ sw, const int32_t* __restrict__ offsets, int G,
+    int extra, uint16_t* __restrict__ y, int64_t N, int64_t K, const int32_t* __restrict__ gidx, int src_rows) {
+  using S = GroupedSmall<WK>;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[S::kLds + kFindLds];
+  RowChunk rc;
+  if ((int)blockIdx.y < extra) {
+    if (!find_chunk(offsets, G, (int)blockIdx.y, reinterpret_cast<int*>(lds + S::kLds), rc)) return;
+  } else {
+    rc.e = (int)blockIdx.y - extra;
+    rc.r0 = offsets[rc.e];
+    rc.r1 = offsets[rc.e + 1];
+    if (rc.r0 >= rc.r1) return;
+    rc.r1 = min(rc.r1, rc.r0 + chunk_size(rc.r1 - rc.r0));
+  }
+  const int n0 = blockIdx.x * S::kRows;
   const int KB = (int)(K / 128);
-  const uint8_t* wbase = qw + ((int64_t)e * N + n0) * K;
-  const float* swrow = sw + ((int64_t)e * (N / 128) + (n0 >> 7)) * KB;
-  auto chunk = [&](auto cfg, int r, int m) {
+  const int m = rc.r1 - rc.r0;
+  const int64_t qw_off = (int64_t)rc.e * N * K, sw_off = (int64_t)rc.e * (N / 128) * KB;
+  if (m > kChunkRows) {
+    if (n0 % S::Wide::BN) return;                  // (its neighbour's tile covers these weight rows)
+    OneJob jobs{TileJob{rc.r0, m, n0, qw_off, sw_off}, false};
+    gemm_tiles<typename S::Wide, true, OneJob, kMx, kGather>(qa, lda, sa, ld_sa, qw, K, sw, KB, y, N, (int)N, KB, jobs,
+                                                             lds, gidx, src_rows);
+    return;
+  }
+  auto chunk = [&](auto cfg) {
     using C = decltype(cfg);
-    const uint8_t* abase = kGather ? qa : qa + (int64_t)r * lda;
-    const float* sbase = kGather ? sa : sa + r;
+    const int lane = threadIdx.x & 63;
     uint32_t arow[C::AO];                        // rows past the end re-read the last
 #pragma unroll
     for (int o = 0; o < C::AO; ++o) {
       const int i = min(o * 8 + (lane >> 3), m - 1);
-      arow[o] = (uint32_t)(kGather ? min(max(gidx[r + i], 0), src_rows - 1) : i) * (uint32_t)lda;
+      arow[o] = (uint32_t)(kGather ? min(max(gidx[rc.r0 + i], 0), src_rows - 1) : i) * (uint32_t)lda;
     }
     const int i = min(lane, m - 1);
-    const uint32_t srow = (uint32_t)(kGather ? min(max(gidx[r + i], 0), src_rows - 1) : i);
-    small_tile<C, kMx>(wbase, (uint32_t)K, swrow, abase, arow, sbase, ld_sa, srow, y + (int64_t)r * N + n0, N, m, KB,
-                       lds);
+    const uint32_t srow = (uint32_t)(kGather ? min(max(gidx[rc.r0 + i], 0), src_rows - 1) : i);
+    small_tile<C, kMx>(qw + qw_off + (int64_t)n0 * K, (uint32_t)K, sw + sw_off + (int64_t)(n0 >> 7) * KB,
+                       kGather ? qa : qa + (int64_t)rc.r0 * lda, arow, kGather ? sa : sa + rc.r0, ld_sa, srow,
+                       y + (int64_t)rc.r0 * N + n0, N, m, KB, lds);
   };
-  for (int r = r0 + 32 * (int)blockIdx.z; r < r1; r += 32 * (int)gridDim.z) {
-    const int m = min(32, r1 - r);
-    if (r >= r0 + 32 * (int)gridDim.z) __syncthreads();   // the last chunk's sums have been read
-    if (m <= 8) chunk(typename G::R8{}, r, m);
-    else if (m <= 16) chunk(typename G::R16{}, r, m);
-    else chunk(typename G::R32{}, r, m);
-  }
+  if (m <= 8) chunk(typename S::R8{});
+  else if (m <= 16) chunk(typename S::R16{});
+  else chunk(typename S::R32{});
 }
 
 }  // namespace fp8rl

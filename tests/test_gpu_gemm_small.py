@@ -85,3 +85,77 @@ def test_grouped_few_rows(fp8rl, counts, n, k):
     close(y, gemm.grouped_gemm_ref_fp64(qa, sa, qw, sw, offsets), "fp32 scales")
     assert torch.equal(y.view(torch.int16), yg.view(torch.int16)), "gathered rows differ"
     close(y2, gemm.grouped_gemm_ref_fp64(qa, p_a, qw, p_w, offsets), "power-of-two scales")
+
+
+def random_experts(rng, g, n, k, rows):
+    """Operands without a quantiser: any finite E4M3 codes are valid ones (many experts, few rows)."""
+    code = lambda *shape: (rng.integers(0, 0x7F, shape) | rng.integers(0, 2, shape) << 7).astype(np.uint8)
+    scale = lambda *shape: np.exp2(rng.uniform(-9, -7, shape)).astype(np.float32)
+    return code(rows, k), scale(k // 128, rows), code(g, n, k), scale(g, n // 128, k // 128)
+
+
+# rows of some experts of G, the others have none: chunks of 128 rows with tails of 1, 8, 32, 33 and 128 rows beside
+# chunks of 32; popular experts first, last and side by side; more than 256 experts (the four waves share the search)
+@pytest.mark.parametrize("g,counts", [
+    (24, {0: 288}), (24, {23: 264, 22: 24}), (48, {5: 257, 6: 129, 7: 128, 8: 33, 9: 1}), (48, {0: 161, 1: 384, 47: 31}),
+    (256, {255: 700, 3: 129, 4: 1}), (257, {256: 650, 255: 64, 0: 33}), (300, {0: 1, 255: 130, 256: 300, 299: 97}),
+    (1024, {1023: 900, 767: 129, 512: 256, 0: 32, 511: 33}), (1024, {}),
+])
+@pytest.mark.parametrize("n,k", [(128, 256), (256, 1152)])
+def test_grouped_popular_experts(fp8rl, g, counts, n, k):
+    announce(f"grouped gemm popular experts {counts} of {g}, n={n} k={k}")
+    if g * n * k > 1 << 27:
+        n = 128
+    counts = counts or {e: 1 + (e % 7 == 0) * 40 for e in range(g)}
+    rng = np.random.default_rng(g + sum(counts.values()) + k)
+    c = np.zeros(g, np.int64)
+    for e, rows in counts.items():
+        c[e] = rows
+    r = int(c.sum())
+    assert r <= 12 * g, "the case is meant for the few-row kernel"
+    offsets = np.concatenate([[0], np.cumsum(c)]).astype(np.int32)
+    qt, st, qw, sw = random_experts(rng, g, n, k, 40)
+    index = rng.integers(0, 40, r).astype(np.int32)
+    qa, sa = np.ascontiguousarray(qt[index]), np.ascontiguousarray(st[:, index])
+    w, s, off = torch.from_numpy(qw).cuda(), torch.from_numpy(sw).cuda(), torch.from_numpy(offsets).cuda()
+    out = torch.full((r + 2, n), 7.0, dtype=torch.bfloat16, device="cuda")
+    fp8rl.fp8rl_grouped_gemm_w8a8_block(torch.from_numpy(qa).cuda(), padded(sa, 3, torch.float32), w, s, off, y=out[:r])
+    yg = fp8rl.fp8rl_grouped_gemm_w8a8_block_gathered(padded(qt, 32, torch.uint8)[:, :k], padded(st, 1, torch.float32),
+                                                      torch.from_numpy(index).cuda(), w, s, off)
+    p_a, p_w = pow2(sa), pow2(sw)
+    y2 = fp8rl.fp8rl_grouped_gemm_w8a8_block_ue8m0(torch.from_numpy(qa).cuda(), torch.from_numpy(p_a).cuda(), w,
+                                                   torch.from_numpy(p_w).cuda(), off)
+    torch.cuda.synchronize()
+    full = np.concatenate([[0], np.cumsum(c[c > 0])]).astype(np.int32)         # (the oracle needs no empty experts)
+    close(out[:r], gemm.grouped_gemm_ref_fp64(qa, sa, qw[c > 0], sw[c > 0], full), "fp32 scales")
+    assert torch.equal(out[:r].view(torch.int16), yg.view(torch.int16)), "gathered rows differ"
+    close(y2, gemm.grouped_gemm_ref_fp64(qa, p_a, qw[c > 0], p_w[c > 0], full), "power-of-two scales")
+    assert torch.all(out[r:] == 7.0), "wrote outside y"
+
+
+def test_one_expert_with_all_rows_is_no_serial_chain(fp8rl):
+    """3072 rows of 256 experts: all in one expert read 1/256 of the weights, so the call may not take as long as with
+    12 rows in each (measured 0.23 of it; 1.14 when a few workgroups walked the expert's rows)."""
+    announce("grouped gemm: one expert with all the rows, timed")
+    g, n, k, rows = 256, 2048, 768, 3072
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    codes = lambda *shape: torch.randint(0, 120, shape, dtype=torch.uint8, device="cuda", generator=gen)
+    qa, qw = codes(rows, k), codes(g, n, k)
+    sa, sw = torch.ones((k // 128, rows), device="cuda"), torch.ones((g, n // 128, k // 128), device="cuda")
+    y = torch.empty((rows, n), dtype=torch.bfloat16, device="cuda")
+
+    def span(counts):
+        off = torch.tensor([0] + torch.tensor(counts).cumsum(0).tolist(), dtype=torch.int32, device="cuda")
+        times = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                fp8rl.fp8rl_grouped_gemm_w8a8_block(qa, sa, qw, sw, off, y=y)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) / 20)
+        return sorted(times)[3]
+
+    even, one = span([rows // g] * g), span([0] * 99 + [rows] + [0] * (g - 100))
+    assert one < 0.6 * even, f"one expert {one * 1e3:.1f} us, spread evenly {even * 1e3:.1f} us"
