@@ -46,13 +46,8 @@ hipError_t launch_gemm_w8a8_block(const uint8_t* qa, int64_t lda, const float* s
                                   uint16_t* y, int64_t ldy, int64_t m, int64_t n, int64_t k,
                                   hipStream_t stream, bool pow2_scales);
 
-// Few tokens: dense products of at most kSmallTokens tokens, and grouped ones of
-// at most kSmallRowsPerExpert rows per expert on average, stream the weights once
-// (gemm_small.hpp) instead of running padded output tiles.  gidx as in the gathered
-// grouped GEMM below, or NULL (then lda = k).
-constexpr int64_t kSmallTokens = 64;
-constexpr int64_t kSmallRowsPerExpert = 12;
-constexpr int64_t kSmallMaxN = int64_t(1) << 24;     // one workgroup per 16-64 weight rows: grid limit
+// The few-token GEMMs (gemm_plan.hpp says when).  gidx as in the gathered grouped GEMM
+// below, or NULL (then lda = k).
 hipError_t launch_gemm_small(const uint8_t* qa, int64_t lda, const float* sa, int64_t ld_sa, const uint8_t* qw,
                              int64_t ldw, const float* sw, uint16_t* y, int64_t ldy, int64_t m, int64_t n, int64_t k,
                              hipStream_t stream, bool pow2_scales);
