@@ -145,15 +145,16 @@ int fp8rl_gemm_w8a8_block(const uint8_t* qa, int64_t lda, const float* sa, int64
  * The same dense product (same operation and arguments as fp8rl_gemm_w8a8_block,
  * section 2.1.1 Eq. (1) and section 2.1.4), for callers that can lend a
  * workspace: shapes whose output tiles are too few to fill the GPU (decode,
- * m of up to a few hundred tokens; for 128 < m <= 256 only when k > 4096, as
- * shorter K ranges run unsplit on 64 x 64 tiles) split the K range over several
+ * 65 to a few hundred tokens, long K) split the K range over several
  * workgroups, which write fp32 partial sums to the workspace; a second kernel
  * adds them in a fixed order and rounds to bf16 once.
  *
- * fp8rl_gemm_w8a8_block_workspace_size: bytes of workspace the split needs for
- * this shape (splits * m * n * 4), 0 when the shape is not split (then
+ * fp8rl_gemm_w8a8_block_workspace_size: bytes of workspace a split of this shape
+ * needs (ranges * m * n * 4), 0 when the shape is never split (then
  * fp8rl_gemm_w8a8_block_ws runs exactly fp8rl_gemm_w8a8_block) or is invalid.
- * A pure function of (m, n, k); no device call.
+ * An upper bound of what a call touches: whether the ranges and their reduction
+ * are run is for the call to choose (below).  A pure function of (m, n, k); no
+ * device call.
  *
  * fp8rl_gemm_w8a8_block_ws: workspace is a DEVICE buffer of workspace_bytes,
  * 16-byte aligned, owned by the caller, no initial contents required; it is
@@ -164,8 +165,9 @@ int fp8rl_gemm_w8a8_block(const uint8_t* qa, int64_t lda, const float* sa, int64
  * workspace not 16-byte aligned.  The split result is deterministic and meets
  * the same tolerance; it is not bit-identical to the unsplit path (the K
  * blocks are summed in a different fp32 order).  Calls of at most 64 tokens, and
- * those whose unsplit tiles are faster than the ranges and their reduction, run
- * fp8rl_gemm_w8a8_block's kernel whatever the workspace, and leave it untouched.
+ * those whose unsplit tiles take less time than the ranges and their reduction
+ * (a function of (m, n, k) too), run fp8rl_gemm_w8a8_block's kernel whatever the
+ * workspace, and leave it untouched.
  */
 int64_t fp8rl_gemm_w8a8_block_workspace_size(int64_t m, int64_t n, int64_t k);
 

@@ -316,7 +316,7 @@ def _gemm(name, qa, sa, qw, sw, y, stream):
 
 
 def fp8rl_gemm_w8a8_block_workspace_size(m: int, n: int, k: int) -> int:
-    """Bytes of workspace fp8rl_gemm_w8a8_block_ws splits K with for this shape (0: no split)."""
+    """Bytes of workspace with which fp8rl_gemm_w8a8_block_ws may split K for this shape (0: never split)."""
     return int(load().fp8rl_gemm_w8a8_block_workspace_size(m, n, k))
 
 

@@ -109,16 +109,13 @@ inline ColumnSplit column_split(int64_t m, int64_t n, int64_t k) {
   return {0, c.tile, whole.tile};
 }
 
-// K ranges of a split product (1: never split).
+// K ranges of a split product, with room for which a caller may lend a workspace (1:
+// never split): only where the 128x128 tiles cover less than half of the CUs, the
+// largest power of two of ranges that keeps tiles x ranges within the CUs (more ranges
+// lose to the fp32 partial sums), each at least 4 K blocks long.
 inline int splitk_ranges(int64_t m, int64_t n, int64_t k) {
-  // Split K only when the 128x128 tiles cover less than half of MI355X's 256
-  // CUs, into the largest power of two of ranges that keeps tiles x splits
-  // within 256, each range at least 4 K blocks long.  (Measured on the decode
-  // linears, M = 256: more ranges lose to the fp32 partial-sum traffic, which
-  // grows with the split.)
   if (m <= 0 || n <= 0 || k <= 0 || (m >= 2048 && n >= 2048)) return 1;
-  // decode batches run unsplit on 64x64 tiles when K is short enough for one
-  // workgroup's K loop (Qwen3-8B qkv, o_proj: K = 4096; down, K = 12288, splits)
+  // (short K on up to two 64x64 tiles per CU: never faster split)
   if (m > 128 && m <= 256 && k <= 4096 && ((m + 63) / 64) * (n / 64) <= 512) return 1;
   const int64_t tiles = ((m + 127) / 128) * (n / 128);
   if (2 * tiles >= kCus) return 1;
@@ -129,17 +126,25 @@ inline int splitk_ranges(int64_t m, int64_t n, int64_t k) {
   return s > 1 ? (int)s : 1;
 }
 
-// Whether the `splits` ranges of splitk_ranges are run, where there is room for their
-// partial sums.  Few tokens need no K ranges across workgroups (measured at M = 64,
-// down: 20.6 us against 20.2 us split with its reduction; every other shape faster), and
-// others only where their ranges, the partial sums (16 MiB: 9 us) and the second launch
-// beat the unsplit tile.  Split / unsplit us: M = 128 down 22.9 / 34, M = 256 down 29.6 /
-// 34; M = 128 qkv 18.7 / 13.5, o_proj 20.5 / 13.1, M = 300 o_proj 23.1 / 15.8, down
-// 42.4 / 38.8.
+// Whether those ranges are run, given the room.  Split: 10 us for the two launches with
+// the pipelines' start and end, 0.45 us per K block of a range and 0.55 us per MiB of
+// partial sums written and read; unsplit: 3 us and the tile's step times.  Few tokens
+// never split.  Measured, us, weights from HBM, split / unsplit:
+//   M            65           100          128          200          256          300
+//   qkv       16.2 / 12.7  17.5 / 12.7  18.7 / 13.9
+//   o_proj    15.7 / 11.9  18.1 / 12.5  21.0 / 13.3                            22.2 / 15.9
+//   down      20.4 / 27.1  21.5 / 30.5  22.9 / 34.1  26.9 / 27.3  28.6 / 32.9  36.8 / 37.8
+//   8192x4096 17.4 / 19.1  18.4 / 20.4  20.1 / 22.4  21.3 / 19.4  22.3 / 22.4  28.2 / 26.3
+//   4096x1024 10.7 / 10.6  11.7 / 10.8  12.3 / 10.8                            15.1 / 10.9
+//   12288x1024 18.1 / 25.2 19.8 / 28.7  21.9 / 32.3  21.2 / 25.6  22.9 / 30.6  20.0 / 29.6
+// (K x N).  Over 13 such layers, 65 .. 800 tokens, the rule's choice is within 0.7 us of
+// the faster one but where the table's step time for the unsplit tile is too high: 1.9
+// us of 28 (8192x4096, M = 300), 2.4 of 18 (6144x2560, M = 129), 3 of 34 (9728x5120, M =
+// 300), 1 to 1.7 of 14 (5760x512, M = 256 .. 360).
 inline bool splitk_pays(int64_t m, int64_t n, int64_t k, int splits) {
   if (splits <= 1 || few_tokens(m, n)) return false;
-  const double kb = (double)(k / 128), mib = (double)(splits * m * n) / (1 << 18);
-  return tile_for(m, n).step * kb > 0.75 * kb / splits + 9.0 * mib / 16.0;
+  const double kb = (double)(k / 128), mib = (double)((int64_t)splits * m * n) / (1 << 18);
+  return 3.0 + tile_for(m, n).step * kb > 10.0 + 0.45 * kb / splits + 0.55 * mib;
 }
 
 }  // namespace fp8rl

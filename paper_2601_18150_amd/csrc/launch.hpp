@@ -56,8 +56,9 @@ hipError_t launch_grouped_small(const uint8_t* qa, int64_t lda, const float* sa,
                                 int64_t n, int64_t k, const int32_t* gidx, int64_t src_rows, hipStream_t stream,
                                 bool pow2_scales);
 
-// Split-K factor the dense GEMM uses for this shape (1: no split); the
-// workspace it needs is splits * m * n fp32 values.
+// K ranges a split of this shape has (1: never split), for which a workspace holds
+// splits * m * n fp32 values; launch_gemm_w8a8_block_splitk runs them where that pays
+// (gemm_plan.hpp) and the unsplit product elsewhere.
 int splitk_factor(int64_t m, int64_t n, int64_t k);
 
 hipError_t launch_gemm_w8a8_block_splitk(const uint8_t* qa, int64_t lda, const float* sa, int64_t ld_sa,

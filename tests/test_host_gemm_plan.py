@@ -44,3 +44,31 @@ def test_every_grid_is_one_that_hip_launches(plan):
     for shape, p in zip(shapes, plan(shapes)):
         if not p.few_tokens:
             assert max(p.first_workgroups, p.rest_workgroups) * 512 < 1 << 32, (shape, p)
+
+
+# (K, N), M, whether the K ranges and their reduction were measured faster than the unsplit tile, by 1 us at least
+@pytest.mark.parametrize("k,n,ms,split", [
+    (4096, 6144, [65, 72, 80, 100, 128], False), (4096, 4096, [65, 72, 80, 90, 100, 112, 128, 300, 360], False),
+    (12288, 4096, [65, 72, 80, 100, 128, 129, 160, 256, 360], True), (8192, 4096, [65, 80, 100, 128], True),
+    (8192, 4096, [200], False), (4096, 1024, [100, 128, 300, 512, 800], False), (12288, 1024, [65, 128, 256, 300, 800], True),
+    (6144, 2560, [160, 200, 256, 300, 360], False), (16384, 2048, [65, 128, 256, 512], True),
+    (2048, 256, [65, 100, 300, 512], False), (28 * 128, 2048, [65, 128, 300], False), (45 * 128, 512, [65, 80, 90, 100], True),
+    (12288, 4096, [1, 8, 33, 64], False),
+])
+def test_k_is_split_where_that_was_measured_faster(plan, k, n, ms, split):
+    for m, p in zip(ms, plan([(m, n, k) for m in ms])):
+        assert p.split == split, (m, n, k, p)
+        assert p.splits > 1 or not split
+
+
+def test_a_split_that_is_run_fits_its_room(plan):
+    """Ranges of at least 4 K blocks, tiles x ranges within the 256 CUs, 16 MiB of partial sums at most."""
+    shapes = [(m, n, k) for m in (65, 100, 128, 129, 255, 300, 512, 1024, 2047, 5000) for n in (128, 256, 640, 1024, 4096, 16384)
+              for k in (512, 1024, 37 * 128, 4096, 12288, 65536)]
+    ran = 0
+    for (m, n, k), p in zip(shapes, plan(shapes)):
+        if p.split:
+            ran += 1
+            assert k // 128 >= 4 * p.splits and p.splits * ((m + 127) // 128) * (n // 128) <= 256
+            assert p.splits * m * n * 4 <= 16 << 20
+    assert ran > 20
