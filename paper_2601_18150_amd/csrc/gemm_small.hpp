@@ -206,9 +206,11 @@ struct GroupedSmall {
   static_assert(R8::kThreads == 256 && Wide::kThreads == 256 && Wide::BN % kRows == 0, "one workgroup for all");
 };
 constexpr int kChunkRows = 32;
-// (one expert of 128 rows, gate_up: four chunks of 32 10.6 us, one wide chunk 12.5; of 256
-// rows: 19.9, wide 18.9)
-constexpr int kWideFrom = 128;
+// (one expert alone, gate_up: of 128 rows four chunks of 32 take 10.6 us, one wide chunk
+// 12.5; of 256 rows 19.9 and 18.9.  Beside others a wide chunk is a long chain: expert
+// block, 190 tokens x 8 by Zipf's law with up to 190 rows in an expert, 126.5 us with wide
+// chunks there, 124.2 without)
+constexpr int kWideFrom = 256;
 constexpr int kWideRows = 128;
 
 // The rows of a chunk: r0 .. r1 - 1, of expert e.
