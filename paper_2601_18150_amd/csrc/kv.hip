@@ -297,6 +297,12 @@ __device__ __forceinline__ v4i16_t to_bf16x4(const uint2& c) { return __builtin_
 
 __device__ __forceinline__ float shfl_xor_f(float v, int m) { return __shfl_xor(v, m, 64); }
 
+// The value that lane kLane of this lane's four neighbours (0-3, 4-7, ..) holds.
+template <int kLane>
+__device__ __forceinline__ float quad_lane(uint32_t v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x55 * kLane, 0xF, 0xF, false));
+}
+
 // Max over the four lanes with the same L % 16 (lane-row swaps, no LDS traffic).
 __device__ __forceinline__ float max_over_rows(float v) {
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -567,14 +573,18 @@ __device__ __forceinline__ void attn_decode_split_of(
     float mm = kNoScore;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, comb[w * kComb + kG * kDim + head]);
+    // expf as in the merge (exact to an ulp far below the maximum too), one per thread: lane
+    // w of each four weighs wave w, and every lane takes the four weights from there
+    static_assert(kWaves == 4, "one lane of four for each wave");
+    const uint32_t mine = __float_as_uint(expf(comb[(threadIdx.x & 3) * kComb + kG * kDim + head] - mm));
+    const float f[kWaves] = {quad_lane<0>(mine), quad_lane<1>(mine), quad_lane<2>(mine), quad_lane<3>(mine)};
     float ls = 0.0f, a0 = 0.0f, a1 = 0.0f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       const float* c = comb + w * kComb;
-      const float f = expf(c[kG * kDim + head] - mm);      // (as in the merge: exact to an ulp far below the maximum too)
-      ls += c[kG * kDim + kG + head] * f;
-      a0 += c[head * kDim + d] * f;
-      a1 += c[head * kDim + d + 1] * f;
+      ls += c[kG * kDim + kG + head] * f[w];
+      a0 += c[head * kDim + d] * f[w];
+      a1 += c[head * kDim + d + 1] * f[w];
     }
     if (max_splits == 1) {                       // the whole sequence: the output itself
       const float f = (v_scale ? v_scale[0] : 1.0f) / ls;
