@@ -280,7 +280,7 @@ def run_dense_ws(fp8rl, qa, sa, qw, sw, ws_bytes=None):
 
 def test_gemm_split_k_decode_layer(fp8rl):
     """The four decode linears through the split-K entry point (workspace pre-filled with NaN:
-    every partial the reduction reads must have been written)."""
+    every partial the reduction reads must have been written; down splits, the others run unsplit)."""
     acts = synth.decode_activations()
     ws = synth.layer_weights(35)
     for name, (k, n) in synth.QWEN3_8B_LINEARS.items():
@@ -289,13 +289,14 @@ def test_gemm_split_k_decode_layer(fp8rl):
         qa, sa = cref.quant_act_token_group128(u16(x))
         qw, sw = cref.quant_weight_block128(u16(ws[name]))
         y, need = run_dense_ws(fp8rl, qa, sa, qw, sw)
-        assert (need > 0) == (name == "down"), (name, need)   # qkv, o_proj: unsplit 64x64 tiles
+        assert (need > 0) == (name == "down"), (name, need)   # qkv, o_proj: unsplit tiles
         check(y, gemm.gemm_ref_fp64(qa, sa, qw, sw), f"split-K {name}")
 
 
 @pytest.mark.parametrize("m,n,k", [(1, 128, 1024), (37, 384, 13 * 128), (100, 256, 2048), (255, 640, 33 * 128)])
 def test_gemm_split_k_ragged(fp8rl, m, n, k):
-    """Ragged M and N tails and a K range that does not divide evenly among the splits."""
+    """Ragged M and N tails through the workspace entry point, for shapes that have room to split (whether they
+    do: test_gemm_split_k_runs_or_leaves_the_workspace)."""
     announce(f"gemm split-K m={m} n={n} k={k}")
     qa, sa, qw, sw = quantised_operands(m, n, k, m * 11 + n + k)
     y, need = run_dense_ws(fp8rl, qa, sa, qw, sw)
@@ -313,6 +314,36 @@ def test_gemm_split_k_short_workspace_runs_unsplit(fp8rl):
     assert need > 1024
     y = run_dense(fp8rl, qa, sa, qw, sw)
     assert torch.equal(y_ws.view(torch.int16), y.view(torch.int16))
+
+
+# shapes above the few-token kernel whose K ranges run (the count of ranges; K blocks that they do not divide evenly), and
+# shapes with room for ranges that run unsplit all the same; checked on the host, test_host_gemm_plan.py
+SPLIT_CASES = [(100, 256, 37 * 128, 9), (255, 640, 61 * 128, 15), (129, 384, 47 * 128, 11), (300, 1024, 96 * 128, 8),
+               (65, 128, 128 * 128, 32)]
+UNSPLIT_CASES = [(37, 384, 13 * 128), (100, 256, 2048), (255, 640, 33 * 128), (300, 1024, 2048)]
+
+
+@pytest.mark.parametrize("m,n,k,ranges", SPLIT_CASES + [(*c, 0) for c in UNSPLIT_CASES])
+def test_gemm_split_k_runs_or_leaves_the_workspace(fp8rl, m, n, k, ranges):
+    """A call that splits writes every partial sum of its workspace, one that does not writes nothing there; the
+    no-allocation entry point gives the same bits either way."""
+    announce(f"gemm split-K m={m} n={n} k={k}, {ranges} ranges")
+    qa, sa, qw, sw = quantised_operands(m, n, k, m * 13 + n + k)
+    need = fp8rl.fp8rl_gemm_w8a8_block_workspace_size(m, n, k)
+    assert need > 0 and (ranges == 0 or need == ranges * m * n * 4)
+    ws = torch.full((need // 4 + 16,), float("nan"), dtype=torch.float32, device="cuda")
+    d = [to_dev(x) for x in (qa, sa, qw, sw)]
+    y = fp8rl.fp8rl_gemm_w8a8_block_ws(*d, ws[:need // 4])
+    scratch = fp8rl.fp8rl_gemm_w8a8_block_noalloc(*d)
+    torch.cuda.synchronize()
+    written = ~torch.isnan(ws)
+    assert torch.all(written[:need // 4] == (ranges > 0)), "partial sums missing" if ranges else "wrote a workspace it does not use"
+    assert not torch.any(written[need // 4:]), "wrote past the workspace"
+    check(y, gemm.gemm_ref_fp64(qa, sa, qw, sw), f"split-K {m}x{n}x{k}")
+    assert torch.equal(scratch.view(torch.int16), y.view(torch.int16)), "static scratch and workspace differ"
+    if ranges == 0:
+        plain = fp8rl.fp8rl_gemm_w8a8_block(*d)
+        assert torch.equal(plain.view(torch.int16), y.view(torch.int16)), "not the unsplit product's bits"
 
 
 def test_gemm_prefill_full_size_every_element(fp8rl):

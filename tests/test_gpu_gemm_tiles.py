@@ -20,17 +20,21 @@ def fp8rl():
     return m
 
 
-@pytest.mark.parametrize("m,n,k", [
-    (65, 128, 128), (100, 256, 384), (129, 1024, 13 * 128), (256, 4096, 9 * 128),      # 64x64, two K groups
-    (300, 4096, 128), (512, 4096, 5 * 128),                                             # 64x128
-    (300, 6144, 256), (257, 5120, 7 * 128),                                             # 128x64
-    (777, 4096, 128), (1000, 4096, 6 * 128),                                            # 128x128, eight waves
-    (200, 24576, 384), (777, 6272, 4 * 128),                                            # 128x256
-    (640, 24704, 128), (600, 24576, 5 * 128),                                           # 256x128, last tile of 128
-    (1300, 6272, 128), (300, 24704, 384),                                               # 256x256, last tile of 128
-    (1400, 12800, 256),                                                                 # persistent 128x128
-    (777, 24576, 9 * 128), (3001, 6272, 7 * 128), (2100, 6144, 1024),                   # columns in two launches
-])
+# (which tile a shape runs on is checked on the host, test_host_gemm_plan.py)
+TILE_CASES = {
+    "64x64": [(65, 128, 128), (100, 256, 384), (129, 1024, 13 * 128), (256, 4096, 9 * 128)],      # two K groups
+    "64x128": [(300, 4096, 128), (512, 4096, 5 * 128), (257, 5120, 7 * 128)],
+    "128x64": [(300, 6144, 256), (257, 5632, 13 * 128)],
+    "128x128": [(777, 4096, 128), (1000, 4096, 6 * 128)],                                          # eight waves
+    "128x256": [(200, 24576, 384), (777, 6272, 4 * 128)],
+    "256x128": [(640, 24704, 128), (600, 24576, 5 * 128)],                                         # last tile of 128
+    "256x256": [(1300, 6272, 128), (300, 24704, 384), (2100, 6144, 1024)],                         # last tile of 128
+    "persistent": [(1400, 12800, 256)],                                                            # 128x128
+    "two launches": [(777, 24576, 9 * 128), (3001, 6272, 7 * 128)],                                # columns
+}
+
+
+@pytest.mark.parametrize("m,n,k", [shape for shapes in TILE_CASES.values() for shape in shapes])
 def test_dense_tile_choices(fp8rl, m, n, k):
     announce(f"gemm tiles m={m} n={n} k={k}")
     qa, sa, qw, sw = operands(np.random.default_rng(m + n + k), m, n, k)
@@ -43,8 +47,7 @@ def test_dense_tile_choices(fp8rl, m, n, k):
     close(out[:m, :n], gemm.gemm_ref_fp64(qa, sa, qw, sw), "fp32 scales")
     assert torch.equal(again.view(torch.int16), out[:m, :n].contiguous().view(torch.int16)), "not deterministic"
     assert torch.all(out[m:] == 7.0) and torch.all(out[:, n:] == 7.0), "wrote outside y"
-    if m * n * k < 2e9:
-        p_a, p_w = pow2(sa), pow2(sw)
-        y2 = fp8rl.fp8rl_gemm_w8a8_block_ue8m0(q, padded(p_a[:, :m], 5, torch.float32), w, torch.from_numpy(p_w).cuda())
-        torch.cuda.synchronize()
-        close(y2, gemm.gemm_ref_fp64(qa, p_a, qw, p_w), "power-of-two scales")
+    p_a, p_w = pow2(sa), pow2(sw)
+    y2 = fp8rl.fp8rl_gemm_w8a8_block_ue8m0(q, padded(p_a[:, :m], 5, torch.float32), w, torch.from_numpy(p_w).cuda())
+    torch.cuda.synchronize()
+    close(y2, gemm.gemm_ref_fp64(qa, p_a, qw, p_w), "power-of-two scales")

@@ -5,6 +5,9 @@ from typing import NamedTuple
 
 import pytest
 
+from tests.test_gpu_gemm import SPLIT_CASES, UNSPLIT_CASES
+from tests.test_gpu_gemm_tiles import TILE_CASES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -72,3 +75,20 @@ def test_a_split_that_is_run_fits_its_room(plan):
             assert k // 128 >= 4 * p.splits and p.splits * ((m + 127) // 128) * (n // 128) <= 256
             assert p.splits * m * n * 4 <= 16 << 20
     assert ran > 20
+
+
+def test_the_gpu_cases_run_on_the_tiles_they_name(plan):
+    for label, shapes in TILE_CASES.items():
+        for shape, p in zip(shapes, plan(shapes)):
+            assert not p.few_tokens
+            assert (p.n1 > 0) == (label == "two launches"), (label, shape, p)
+            assert label == "two launches" or p.rest == label, (label, shape, p)
+    assert set(TILE_CASES) == {"64x64", "64x128", "128x64", "128x128", "128x256", "256x128", "256x256", "persistent", "two launches"}
+
+
+def test_the_gpu_split_cases_are_split(plan):
+    for (m, n, k, ranges), p in zip(SPLIT_CASES, plan([c[:3] for c in SPLIT_CASES])):
+        assert p.split and p.splits == ranges, (m, n, k, p)
+    for shape, p in zip(UNSPLIT_CASES, plan(UNSPLIT_CASES)):
+        assert not p.split, (shape, p)
+    assert any(r % 2 and k // 128 % r for _, _, k, r in SPLIT_CASES), "an odd number of uneven ranges"
