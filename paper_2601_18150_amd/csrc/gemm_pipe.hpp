@@ -17,8 +17,10 @@
 // WK groups of waves may split the K blocks of one tile (group g takes blocks g,
 // g + WK, ...), each with a ring of its own, so that a small tile has two waves per
 // SIMD; their sums are added in LDS in order.
-// What is left bounds the DMA: a CU takes 45-55 bytes per ns for any of these tiles
-// with weights from HBM (64x64 alone, no MFMA: 11.3 us of the 13.2 us call).
+// What is left is mostly the DMA with weights from HBM, alone (no MFMA) 40 to 47 bytes
+// per ns and busy CU: 12.6 of the 13.9 us of a 64x64 call (M = 256, o_proj), 16.8 of 19.6
+// (64x128, qkv), 39.9 of 45.5 (128x256, gate_up); on 128x128 tiles (M = 777, o_proj) 17.6
+// of 26.2, and the loop without DMA takes 20.2.
 #pragma once
 
 #include "gemm_core.hpp"

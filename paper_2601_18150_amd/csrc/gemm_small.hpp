@@ -7,8 +7,8 @@
 // K loop has no barrier, each wave waits for its own DMA only, and a slot is
 // refilled as soon as its fragments are in registers.  (Fragments loaded straight
 // from global memory need no LDS, but adjacent lanes then hold different rows:
-// four cache lines per quad of lanes, measured at a quarter of the DMA's rate,
-// which reads whole 128-byte lines, eight lanes a row.)
+// four cache lines per quad of lanes, 38 bytes per ns and CU from the L2 where whole
+// 128-byte lines, eight lanes a row as the DMA reads them, reach 130.)
 // The WK waves of a workgroup split the K blocks of the same rows (wave w takes
 // blocks w, w + WK, ...: together they read whole runs of each weight row) and
 // add their fp32 sums through LDS in a fixed order, so that even a narrow layer
