@@ -328,8 +328,9 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
     const int n_valid = n_valid_of(cur);
     // (kCross) a wave none of whose tokens exist only moves data: a ragged tile's idle
     // half leaves the matrix cores and the LDS to the workgroup it shares the CU with
-    // (expert block, gate_up, us without / with: 4096 tokens 177 / 177, 1024 99.0 / 95.4,
-    // 300 81.7 / 77.9; not moving the missing rows either was slower, 99.5 / 83)
+    // (grouped, Zipf routing, gate_up / down, us without / with: 4096 tokens 171.5 / 167.5
+    // and 103.4 / 101.7, 1024 94.4 / 91.4 and 57.0 / 55.8, 300 75.1 / 73.6; not moving the
+    // missing rows either was slower, 99.5 / 83 at 1024 and 300)
     const bool idle = kCross && wm * C::WTM >= cur.m_valid;
     const uint8_t* wbase = qw + cur.qw_off + (int64_t)cur.n0 * ldw;
     const uint8_t* abase = kGather ? qa : qa + (int64_t)cur.row_lo * lda;
@@ -342,31 +343,29 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
 #pragma unroll
       for (int j = 0; j < C::TM; ++j) acc[i][j] = (v4f32){0.f, 0.f, 0.f, 0.f};
 
-    for (int kb = 0; kb < KB; ++kb) {
-      // this step's DMA (and a previous tile's output stores)
-      wait_vmcnt<0>();
-      lds_barrier();
-
-      // refill the slot of step s-1 with step s+1: the next K block of this
-      // tile or, with kCross after its last, the first K block of the next tile
-      // (if any).  With 8
-      // sub-tile rows per wave the DMA instructions are spread over the first
-      // half of the sub-tile loop below (issued all at once they stall the wave
-      // on a full address queue, issued later they arrive after the next
-      // barrier); with fewer, all are issued with the first one (measured
-      // fastest for the 128x128 tiles).
-      const bool last = kb + 1 == KB;
-      const bool refill = !last || has_nxt;
-      uint8_t* dslot = lds + (slot ^ 1) * C::kStageBytes;
+    // The refill of the slot of step s-1 with step s+1: the next K block of this tile or,
+    // with kCross after its last, the first K block of the next tile (if any).
+    struct Refill {
+      bool on, last;
+      uint8_t* slot;
+      __amdgpu_buffer_rsrc_t w, a;
+      uint32_t soff;
+      const float* sa;
+    };
+    auto refill_of = [&](int kb) {
+      Refill f;
+      f.last = kb + 1 == KB;
+      f.on = !f.last || has_nxt;
+      f.slot = lds + (slot ^ 1) * C::kStageBytes;
       const uint8_t* dwb = wbase;
       const uint8_t* dab = abase;
-      uint32_t dsoff = (kb + 1) * 128;
-      const float* dsa = sa_lane + (int64_t)(kb + 1) * ld_sa;
+      f.soff = (kb + 1) * 128;
+      f.sa = sa_lane + (int64_t)(kb + 1) * ld_sa;
       if constexpr (kCross) {
-        if (last) {
+        if (f.last) {
           dwb = qw + nxt.qw_off + (int64_t)nxt.n0 * ldw;
           dab = kGather ? qa : qa + (int64_t)nxt.row_lo * lda;
-          dsoff = 0;
+          f.soff = 0;
           if constexpr (kGather) {
             // the next tile's source rows, loaded a tile ago (retired by this
             // step's vmcnt(0)): its DMA offsets and scale row
@@ -374,29 +373,54 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
               clamp_rows(rs_n, srow_n);
               dma_offsets(goff_n, n_valid_of(nxt), nxt.m_valid, rs_n);
             }
-            dsa = sa + srow_n;
+            f.sa = sa + srow_n;
           } else {
-            dsa = sa_lane_of(nxt);
+            f.sa = sa_lane_of(nxt);
           }
         }
       }
-      const __amdgpu_buffer_rsrc_t rw = buffer_rsrc(dwb), ra = buffer_rsrc(dab);
+      f.w = buffer_rsrc(dwb);
+      f.a = buffer_rsrc(dab);
+      return f;
+    };
+    auto refill_octet = [&](const Refill& f, int i) {
+      const int o = wave + i * C::kWaves;
+      uint32_t off = goff[i];
+      if constexpr (kCross) off = f.last ? goff_n[i] : goff[i];
+      lds_dma16(o < C::BN / 8 ? f.w : f.a, off, f.soff, f.slot + o * 1024);
+    };
+    auto refill_scales = [&](const Refill& f) { lds_dma4(f.sa, f.slot + C::kWBytes + C::kABytes + wave * 256); };
 
+    // (a loop of its own: as a branch in the loop below it cost the tiles without an idle
+    // wave up to a tenth, us in the loop / here: 48 tiles of K = 2048 17.0 / 15.4, 5 of K =
+    // 4096 28.8 / 25.7, 128 experts of 256 rows 153.8 / 151.0)
+    if (idle) {
+      for (int kb = 0; kb < KB; ++kb) {
+        wait_vmcnt<0>();
+        lds_barrier();
+        const Refill f = refill_of(kb);
+        if (f.on) {
+#pragma unroll
+          for (int i = 0; i < C::kLoadsPerWave; ++i) refill_octet(f, i);
+          if (sdma) refill_scales(f);
+        }
+        slot ^= 1;
+      }
+    }
+    for (int kb = idle ? KB : 0; kb < KB; ++kb) {
+      // this step's DMA (and a previous tile's output stores)
+      wait_vmcnt<0>();
+      lds_barrier();
+
+      // With 8 sub-tile rows per wave the DMA instructions are spread over the first
+      // half of the sub-tile loop below (issued all at once they stall the wave
+      // on a full address queue, issued later they arrive after the next
+      // barrier); with fewer, all are issued with the first one (measured
+      // fastest for the 128x128 tiles).
+      const Refill refill = refill_of(kb);
       constexpr int kDmaSpread = C::TN >= 8 ? C::TN / 2 : 1;   // sub-tile rows that carry DMA issue
       const uint8_t* st = lds + slot * C::kStageBytes;
       const float* sts = reinterpret_cast<const float*>(st + C::kWBytes + C::kABytes) + wm * C::WTM + (lane & 15);
-      if (idle) {
-        if (refill) {
-#pragma unroll
-          for (int i = 0; i < C::kLoadsPerWave; ++i) {
-            const int o = wave + i * C::kWaves;
-            lds_dma16(o < C::BN / 8 ? rw : ra, kCross && last ? goff_n[i] : goff[i], dsoff, dslot + o * 1024);
-          }
-          if (sdma) lds_dma4(dsa, dslot + C::kWBytes + C::kABytes + wave * 256);
-        }
-        slot ^= 1;
-        continue;
-      }
       float sc[C::TM];
       int se[C::TM];
       int sw_e8 = 0;
@@ -426,14 +450,9 @@ __device__ __forceinline__ void gemm_tiles(const uint8_t* __restrict__ qa, int64
       for (int tn = 0; tn < C::TN; ++tn) {
 #pragma unroll
         for (int i = 0; i < C::kLoadsPerWave; ++i) {
-          if ((i * kDmaSpread) / C::kLoadsPerWave == tn && refill) {
-            const int o = wave + i * C::kWaves;
-            uint32_t off = goff[i];
-            if constexpr (kCross) off = last ? goff_n[i] : goff[i];
-            lds_dma16(o < C::BN / 8 ? rw : ra, off, dsoff, dslot + o * 1024);
-          }
+          if ((i * kDmaSpread) / C::kLoadsPerWave == tn && refill.on) refill_octet(refill, i);
         }
-        if (tn == 0 && sdma && refill) lds_dma4(dsa, dslot + C::kWBytes + C::kABytes + wave * 256);
+        if (tn == 0 && sdma && refill.on) refill_scales(refill);
         v8i32 af_next = af;
         if (tn + 1 < C::TN) af_next = lds_frag2(stw + (tn + 1) * 16 * 128, f0, f1);
         if constexpr (kMx) {
