@@ -164,10 +164,10 @@ int fp8rl_gemm_w8a8_block(const uint8_t* qa, int64_t lda, const float* sa, int64
  * or a NULL workspace with workspace_bytes > 0, FP8RL_ERR_MISALIGNED for a
  * workspace not 16-byte aligned.  The split result is deterministic and meets
  * the same tolerance; it is not bit-identical to the unsplit path (the K
- * blocks are summed in a different fp32 order).  Calls of at most 64 tokens, and
- * those whose unsplit tiles take less time than the ranges and their reduction
- * (a function of (m, n, k) too), run fp8rl_gemm_w8a8_block's kernel whatever the
- * workspace, and leave it untouched.
+ * blocks are summed in a different fp32 order).  Calls whose unsplit
+ * kernel takes less time than the ranges and their reduction (a function of (m, n, k)
+ * too; all of at most 64 tokens with k <= 12288) run fp8rl_gemm_w8a8_block's kernel
+ * whatever the workspace, and leave it untouched.
  */
 int64_t fp8rl_gemm_w8a8_block_workspace_size(int64_t m, int64_t n, int64_t k);
 

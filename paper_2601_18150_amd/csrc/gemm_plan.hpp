@@ -126,10 +126,14 @@ inline int splitk_ranges(int64_t m, int64_t n, int64_t k) {
   return s > 1 ? (int)s : 1;
 }
 
-// Whether those ranges are run, given the room.  Split: 10 us for the two launches with
-// the pipelines' start and end, 0.45 us per K block of a range and 0.55 us per MiB of
-// partial sums written and read; unsplit: 3 us and the tile's step times.  Few tokens
-// never split.  Measured, us, weights from HBM, split / unsplit:
+// Whether those ranges are run, given the room: a cost in us for each side, fitted to the
+// layers below and others, 65 .. 800 tokens, and to 8 .. 64 tokens with K = 4096 .. 24576,
+// weights from HBM.  Split: 7.8 for the two launches with the pipelines' start and end,
+// 0.65 per K block of a range, 0.5 per MiB of partial sums written and read, 0.2 per range
+// that the reduction adds, and no less than 11 beside the weights at 5.5 TB/s.  Unsplit: 3
+// and the tile's step times, or for few tokens 2.5 and a step that grows with the tokens
+// and rows (never up to 16 tokens, where eight waves split K already, nor up to K = 12288,
+// where the two are within 1.8 us of each other).  Split / unsplit:
 //   M            65           100          128          200          256          300
 //   qkv       16.2 / 12.7  17.5 / 12.7  18.7 / 13.9
 //   o_proj    15.7 / 11.9  18.1 / 12.5  21.0 / 13.3                            22.2 / 15.9
@@ -137,14 +141,26 @@ inline int splitk_ranges(int64_t m, int64_t n, int64_t k) {
 //   8192x4096 17.4 / 19.1  18.4 / 20.4  20.1 / 22.4  21.3 / 19.4  22.3 / 22.4  28.2 / 26.3
 //   4096x1024 10.7 / 10.6  11.7 / 10.8  12.3 / 10.8                            15.1 / 10.9
 //   12288x1024 18.1 / 25.2 19.8 / 28.7  21.9 / 32.3  21.2 / 25.6  22.9 / 30.6  20.0 / 29.6
-// (K x N).  Over 13 such layers, 65 .. 800 tokens, the rule's choice is within 0.7 us of
-// the faster one but where the table's step time for the unsplit tile is too high: 1.9
-// us of 28 (8192x4096, M = 300), 2.4 of 18 (6144x2560, M = 129), 3 of 34 (9728x5120, M =
-// 300), 1 to 1.7 of 14 (5760x512, M = 256 .. 360).
-inline bool splitk_pays(int64_t m, int64_t n, int64_t k, int splits) {
-  if (splits <= 1 || few_tokens(m, n)) return false;
+//   M            16           32           40           64
+//   down      18.8 / 14.3  18.5 / 15.9  18.9 / 18.4  19.8 / 21.1   (always unsplit)
+//   16384x2048 17.5 / 12.8 17.0 / 15.9  17.5 / 19.4  18.1 / 21.9
+//   24576x1024 20.8 / 17.9 20.2 / 23.4  21.3 / 28.5  22.0 / 33.4
+// (K x N).  Where the rule takes the slower side it loses at most 1.7 us or 10%, but for 2.4
+// and 3 us (6144x2560, M = 129; 9728x5120, M = 300) and, with 200 MB of weights, 6 (24576x8192,
+// M = 48).
+inline double split_cost(int64_t m, int64_t n, int64_t k, int splits) {
   const double kb = (double)(k / 128), mib = (double)((int64_t)splits * m * n) / (1 << 18);
-  return 3.0 + tile_for(m, n).step * kb > 10.0 + 0.45 * kb / splits + 0.55 * mib;
+  const double ranges = 7.8 + 0.65 * kb / splits + 0.5 * mib + 0.2 * splits;
+  const double stream = 11.0 + (double)n * (double)k / 5.5e6;
+  return ranges > stream ? ranges : stream;
+}
+
+inline bool splitk_pays(int64_t m, int64_t n, int64_t k, int splits) {
+  const double kb = (double)(k / 128);
+  if (splits <= 1) return false;
+  if (few_tokens(m, n))
+    return m > 16 && kb > 96 && 2.5 + kb * (0.045 + 0.0017 * (double)m + 1.2e-5 * (double)n) > split_cost(m, n, k, splits);
+  return 3.0 + tile_for(m, n).step * kb > split_cost(m, n, k, splits);
 }
 
 }  // namespace fp8rl

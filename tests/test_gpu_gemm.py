@@ -316,10 +316,11 @@ def test_gemm_split_k_short_workspace_runs_unsplit(fp8rl):
     assert torch.equal(y_ws.view(torch.int16), y.view(torch.int16))
 
 
-# shapes above the few-token kernel whose K ranges run (the count of ranges; K blocks that they do not divide evenly), and
-# shapes with room for ranges that run unsplit all the same; checked on the host, test_host_gemm_plan.py
+# shapes whose K ranges run (the count of ranges; K blocks that they do not divide evenly), above the few tokens and with
+# so many K blocks that few tokens split too, and shapes with room for ranges that run unsplit all the same; checked on
+# the host, test_host_gemm_plan.py
 SPLIT_CASES = [(100, 256, 37 * 128, 9), (255, 640, 61 * 128, 15), (129, 384, 47 * 128, 11), (300, 1024, 96 * 128, 8),
-               (65, 128, 128 * 128, 32)]
+               (65, 128, 128 * 128, 32), (64, 256, 192 * 128, 48), (48, 384, 170 * 128, 42)]
 UNSPLIT_CASES = [(37, 384, 13 * 128), (100, 256, 2048), (255, 640, 33 * 128), (300, 1024, 2048)]
 
 

@@ -56,7 +56,8 @@ def test_every_grid_is_one_that_hip_launches(plan):
     (8192, 4096, [200], False), (4096, 1024, [100, 128, 300, 512, 800], False), (12288, 1024, [65, 128, 256, 300, 800], True),
     (6144, 2560, [160, 200, 256, 300, 360], False), (16384, 2048, [65, 128, 256, 512], True),
     (2048, 256, [65, 100, 300, 512], False), (28 * 128, 2048, [65, 128, 300], False), (45 * 128, 512, [65, 80, 90, 100], True),
-    (12288, 4096, [1, 8, 33, 64], False),
+    (12288, 4096, [1, 8, 16, 32, 64], False), (16384, 2048, [40, 48, 64], True), (24576, 1024, [32, 40, 64], True),
+    (24576, 4096, [40, 64], True), (24576, 4096, [8, 16, 17, 24], False), (8192, 4096, [8, 33, 64], False), (16384, 1024, [8, 16, 24], False),
 ])
 def test_k_is_split_where_that_was_measured_faster(plan, k, n, ms, split):
     for m, p in zip(ms, plan([(m, n, k) for m in ms])):
