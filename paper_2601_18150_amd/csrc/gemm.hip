@@ -20,6 +20,7 @@ namespace {
 using CfgLarge = GemmCfg<256, 256, 2, 4, 2>;   // 512 threads, wave tile 128(n) x 64(m), 130 KiB LDS
 using CfgSmall = GemmCfg<128, 128, 2, 2, 2>;   // 256 threads, wave tile 64 x 64, 65 KiB LDS
 using Cfg64x64 = GemmCfg<64, 64, 2, 2, 4>;     // two groups: 512 threads, wave tile 32 x 32, 130 KiB LDS
+using Cfg64x64Short = GemmCfg<64, 64, 2, 2, 3>; // one group: 256 threads, wave tile 32 x 32, 50 KiB LDS
 using Cfg64x128 = GemmCfg<64, 128, 2, 2, 3>;   // two groups: 512 threads, wave tile 32 x 64, 147 KiB LDS
 using Cfg128x64 = GemmCfg<128, 64, 2, 2, 3>;   // two groups: 512 threads, wave tile 64 x 32, 146 KiB LDS
 using Cfg128x128 = GemmCfg<128, 128, 2, 4, 4>; // 512 threads, wave tile 64 x 32, 130 KiB LDS
@@ -319,6 +320,7 @@ hipError_t launch_tile(Tile tile, const uint8_t* qa, int64_t lda, const float* s
 #define FP8RL_PIPE(C, WK) return launch_pipe<C, WK, kMx>(qa, lda, sa, ld_sa, qw, ldw, sw, y, ldy, m, n, k, stream)
   switch (tile) {
     case Tile::k64x64: FP8RL_PIPE(Cfg64x64, 2);
+    case Tile::k64x64Short: FP8RL_PIPE(Cfg64x64Short, 1);
     case Tile::k64x128: FP8RL_PIPE(Cfg64x128, 2);
     case Tile::k128x64: FP8RL_PIPE(Cfg128x64, 2);
     case Tile::k128x128: FP8RL_PIPE(Cfg128x128, 1);

@@ -19,7 +19,7 @@ inline bool few_tokens(int64_t m, int64_t n) { return m <= kSmallTokens && n < k
 
 // Dense products are one round or several of tiles over the 256 CUs, and a tile's
 // time is its K blocks times a step time that hardly depends on the shape; so the
-// tile is the one with the smallest (rounds x step time).  Step times (us per
+// tile is the one with the smallest (rounds x step time), above kShortK K blocks.  Step times (us per
 // 128-wide K block and round, Qwen3-8B linears, 80 .. 2000 tokens, weights from HBM;
 // about 3 us per call besides):
 //   64x64      0.32   gemm_pipe, two wave groups split K
@@ -35,7 +35,7 @@ inline bool few_tokens(int64_t m, int64_t n) { return m <= kSmallTokens && n < k
 // o_proj 31.4 -> 23.2, down 86.3 -> 60.5; M = 2000 qkv 64.8 -> 53.4, gate_up 228.7 ->
 // 183.8; M = 256 o_proj 15.9 -> 13.2, qkv 21.2 -> 18.6.
 // Tiles are BN x BM, in the order that breaks ties.
-enum class Tile { k64x64, k64x128, k128x64, k128x128, k128x256, k256x128, k256x256, kPersistent };
+enum class Tile { k64x64, k64x128, k128x64, k128x128, k128x256, k256x128, k256x256, kPersistent, k64x64Short };
 
 struct TileChoice {
   Tile tile;
@@ -78,6 +78,34 @@ inline TileChoice tile_for(int64_t m, int64_t n) {
   return best;
 }
 
+// Up to four K blocks a step time says little: a call is its launch, the tiles' prologues
+// and ends, and the output.  Three kernels are left there: 64x64 tiles of one wave group and
+// a 3-slot ring, three workgroups per CU, which the two groups' sums would only hold up; the
+// persistent 128x128; and 256x256.  Their times in us, with KB K blocks, R rounds of 256
+// tiles and the padded output in millions of elements, fitted to 226 shapes of 65 .. 8192
+// tokens and N = 128 .. 24576 (within 2 to 3% at the median); the choice is on average 0.4%
+// from the fastest of all nine kernels, at most 13%.  By rounds x step time / now, us: 148 x
+// 2688 x 384 4.4 / 4.1, 222 x 5504 x 384 6.0 / 5.1, 1076 x 3840 x 256 8.8 / 6.9, 1382 x 5248
+// x 512 9.9 / 8.9, 6355 x 5248 x 128 25.0 / 17.0.
+constexpr int64_t kShortK = 4;
+
+inline Tile short_tile(int64_t m, int64_t n, int64_t kb) {
+  const auto padded = [&](int64_t bm, int64_t bn) {
+    return (double)((m + bm - 1) / bm * bm) * (double)((n + bn - 1) / bn * bn) / 1e6;
+  };
+  const auto rounds = [&](int64_t bm, int64_t bn) {
+    return (double)((((m + bm - 1) / bm) * ((n + bn - 1) / bn) + kCus - 1) / kCus);
+  };
+  const double k = (double)kb;
+  const double small = 2.7 + 0.35 * k + (rounds(64, 64) - 1) * 0.16 * k + 0.46 * padded(64, 64);
+  const double large = 4.8 + 1.3 * k + (rounds(256, 256) - 1) * (2.4 + 1.6 * k) + 0.26 * padded(256, 256);
+  const double halves = rounds(128, 128);          // (512 workgroups are resident)
+  const double persistent = 3.6 + 0.7 * k + (halves > 1 ? 0.2 + 0.25 * k : 0.0) +
+                            (halves > 2 ? (halves - 2) * (0.6 + 0.55 * k) : 0.0) + 0.18 * padded(128, 128);
+  if (small < large && small < persistent && ((m + 63) / 64) * (n / 64) <= kMaxTiles) return Tile::k64x64Short;
+  return large < persistent && ((m + 255) / 256) * ((n + 255) / 256) <= kMaxTiles ? Tile::k256x256 : Tile::kPersistent;
+}
+
 // A nearly empty last round costs almost as much as a full one.  Where that is dear,
 // the first n1 output columns run as whole rounds of 256x256 tiles and the others as a
 // product of their own with the tile that suits them (n1 = 0: one launch for all), if
@@ -94,6 +122,7 @@ struct ColumnSplit {
 
 inline ColumnSplit column_split(int64_t m, int64_t n, int64_t k) {
   const double kb = (double)(k / 128);
+  if (k / 128 <= kShortK) return {0, Tile::k256x256, short_tile(m, n, k / 128)};
   const TileChoice whole = tile_for(m, n);
   constexpr TileCost c = kTileCosts[sizeof(kTileCosts) / sizeof(kTileCosts[0]) - 1];
   static_assert(c.tile == Tile::k256x256, "the last entry");

@@ -17,13 +17,14 @@ static const char* name(Tile t) {
     case Tile::k256x128: return "256x128";
     case Tile::k256x256: return "256x256";
     case Tile::kPersistent: return "persistent";
+    case Tile::k64x64Short: return "64x64-short";
   }
   return "?";
 }
 
 static long long workgroups(Tile t, int64_t m, int64_t n) {
   for (const TileCost& c : kTileCosts)
-    if (c.tile == t) return tile_count(c, m, n);
+    if (c.tile == t || (c.tile == Tile::k64x64 && t == Tile::k64x64Short)) return tile_count(c, m, n);
   return 0;   // persistent: the resident ones
 }
 

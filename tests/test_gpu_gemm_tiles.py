@@ -1,6 +1,6 @@
 """The dense GEMM across its tile choices (64x64 to 256x256, one tile per workgroup and persistent): ragged last
-tiles in both directions, fewer K blocks than ring slots or wave groups, odd K block counts, padded operands.  Pass
-criterion per element as in test_gpu_gemm.py."""
+tiles in both directions, fewer K blocks than ring slots, odd K block counts (uneven wave groups), padded operands.
+Pass criterion per element as in test_gpu_gemm.py."""
 import numpy as np
 import pytest
 import torch
@@ -22,15 +22,18 @@ def fp8rl():
 
 # (which tile a shape runs on is checked on the host, test_host_gemm_plan.py)
 TILE_CASES = {
-    "64x64": [(65, 128, 128), (100, 256, 384), (129, 1024, 13 * 128), (256, 4096, 9 * 128)],      # two K groups
-    "64x128": [(300, 4096, 128), (512, 4096, 5 * 128), (257, 5120, 7 * 128)],
-    "128x64": [(300, 6144, 256), (257, 5632, 13 * 128)],
-    "128x128": [(777, 4096, 128), (1000, 4096, 6 * 128)],                                          # eight waves
-    "128x256": [(200, 24576, 384), (777, 6272, 4 * 128)],
-    "256x128": [(640, 24704, 128), (600, 24576, 5 * 128)],                                         # last tile of 128
-    "256x256": [(1300, 6272, 128), (300, 24704, 384), (2100, 6144, 1024)],                         # last tile of 128
-    "persistent": [(1400, 12800, 256)],                                                            # 128x128
-    "two launches": [(777, 24576, 9 * 128), (3001, 6272, 7 * 128)],                                # columns
+    # up to four K blocks (and above, where K = 5 * 128)
+    "64x64-short": [(65, 128, 128), (100, 256, 384), (65, 128, 512), (257, 640, 256), (129, 2688, 384)],   # one wave group
+    "persistent": [(1400, 12800, 256), (200, 24576, 512), (6355, 640, 128), (1570, 12160, 5 * 128)],       # 128x128
+    "256x256": [(2100, 6272, 384), (1300, 6272, 5 * 128), (300, 24704, 5 * 128), (2100, 6144, 1024)],      # last tile of 128
+    # above (two wave groups split K in the first three)
+    "64x64": [(65, 128, 5 * 128), (129, 1024, 13 * 128), (256, 4096, 9 * 128)],
+    "64x128": [(300, 4096, 5 * 128), (512, 4096, 5 * 128), (257, 5120, 7 * 128)],
+    "128x64": [(300, 6144, 6 * 128), (257, 5632, 13 * 128)],
+    "128x128": [(777, 4096, 5 * 128), (1000, 4096, 6 * 128)],                                              # eight waves
+    "128x256": [(200, 24576, 5 * 128), (777, 6272, 6 * 128)],
+    "256x128": [(640, 24704, 5 * 128), (600, 24576, 6 * 128)],                                             # last tile of 128
+    "two launches": [(777, 24576, 9 * 128), (3001, 6272, 7 * 128), (1400, 12800, 5 * 128)],                # columns
 }
 
 

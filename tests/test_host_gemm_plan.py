@@ -84,7 +84,7 @@ def test_the_gpu_cases_run_on_the_tiles_they_name(plan):
             assert not p.few_tokens
             assert (p.n1 > 0) == (label == "two launches"), (label, shape, p)
             assert label == "two launches" or p.rest == label, (label, shape, p)
-    assert set(TILE_CASES) == {"64x64", "64x128", "128x64", "128x128", "128x256", "256x128", "256x256", "persistent", "two launches"}
+    assert set(TILE_CASES) == {"64x64-short", "64x64", "64x128", "128x64", "128x128", "128x256", "256x128", "256x256", "persistent", "two launches"}
 
 
 def test_the_gpu_split_cases_are_split(plan):
